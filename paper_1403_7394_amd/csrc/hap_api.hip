@@ -1624,7 +1624,7 @@ hap_status hap_mlp_workspace_size(int32_t n_in, int32_t hidden, int32_t n_out, i
     if (!bytes) return fail_arg("hap_mlp_workspace_size: null pointer");
     if (!mlp_dims_ok(n_in, hidden, n_out) || rows < 0 || rows > INT32_MAX)
         return fail_arg("hap_mlp_workspace_size: bad sizes");
-    *bytes = hap::mlp_layout(n_in, hidden, n_out, rows).bytes;
+    *bytes = hap::mlp_workspace_bytes(n_in, hidden, n_out, rows);
     return HAP_OK;
 }
 
@@ -1655,7 +1655,7 @@ hap_status hap_mlp_loss_grad(const float *params, int32_t n_in, int32_t hidden, 
     const hap::MlpLayout lo = hap::mlp_layout(n_in, hidden, n_out, rows);
     if (workspace_bytes < lo.bytes) return fail_arg("hap_mlp_loss_grad: workspace too small");
     hipError_t e = hap::mlp_loss_grad(lo, n_in, hidden, n_out, precision == HAP_BF16, params, X, ldx, T, ldt,
-                                      (int)rows, grad, loss, (char *)workspace, (hipStream_t)stream);
+                                      (int)rows, grad, loss, (char *)workspace, workspace_bytes, (hipStream_t)stream);
     if (e != hipSuccess) return fail_hip(e, "hap_mlp_loss_grad");
     return HAP_OK;
 }
@@ -1687,18 +1687,11 @@ hap_status hap_mlp_train(float *params, float *opt_state, int32_t n_in, int32_t 
     if (workspace_bytes < lo.bytes) return fail_arg("hap_mlp_train: workspace too small");
     char *ws = (char *)workspace;
     hipStream_t st = (hipStream_t)stream;
-    float *Xb = (float *)(ws + lo.Xb), *Tb = (float *)(ws + lo.Tb), *G = (float *)(ws + lo.G);
-    double *loss = (double *)(ws + lo.loss);
     for (int64_t s = 0; s < steps; ++s) {
-        const int32_t *ix = idx + s * batch;
-        hipError_t e = hap::mlp_gather(X, ldx, n_in, ix, (int)batch, (int)rows, Xb, st);
-        if (e == hipSuccess) e = hap::mlp_gather(T, ldt, n_out, ix, (int)batch, (int)rows, Tb, st);
-        if (e == hipSuccess)
-            e = hap::mlp_loss_grad(lo, n_in, hidden, n_out, precision == HAP_BF16, params, Xb, n_in, Tb, n_out,
-                                   (int)batch, G, loss_hist ? loss_hist + s : loss, ws, st);
-        if (e == hipSuccess)
-            e = hap::mlp_adam(params, G, opt_state, opt_state + lo.count, lo.count, step0 + s + 1, lr, 0.9, 0.999,
-                              1e-8, st);
+        const hipError_t e = hap::mlp_train_step(lo, n_in, hidden, n_out, precision == HAP_BF16, params, opt_state,
+                                                 opt_state + lo.count, step0 + s + 1, X, ldx, T, ldt, (int)rows,
+                                                 idx + s * batch, (int)batch, lr, loss_hist ? loss_hist + s : nullptr, ws,
+                                                 workspace_bytes, st);
         if (e != hipSuccess) return fail_hip(e, "hap_mlp_train");
     }
     return HAP_OK;

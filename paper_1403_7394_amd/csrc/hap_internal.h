@@ -252,15 +252,22 @@ struct MlpLayout {
     size_t Xb, Tb, H1, H2, Y, dY, dH2, dH1, G, loss, bytes;
 };
 MlpLayout mlp_layout(int n_in, int hidden, int n_out, int64_t rows);
+// Workspace with which every path runs (at least the layout's bytes; with only those the training
+// of a batch may have to go layer by layer, which gives the same results).
+size_t mlp_workspace_bytes(int n_in, int hidden, int n_out, int64_t rows);
 hipError_t mlp_forward(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, const float *P,
                        const float *X, int64_t ldx, int rows, float *Y, int64_t ldy, char *ws, hipStream_t st);
 hipError_t mlp_loss_grad(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, const float *P,
                          const float *X, int64_t ldx, const float *T, int64_t ldt, int rows, float *G, double *loss,
-                         char *ws, hipStream_t st);
+                         char *ws, size_t ws_bytes, hipStream_t st);
 hipError_t mlp_adam(float *P, const float *G, float *M, float *V, int64_t count, int64_t step, double lr, double b1,
                     double b2, double eps, hipStream_t st);
-hipError_t mlp_gather(const float *X, int64_t ldx, int w, const int32_t *idx, int rows, int x_rows, float *out,
-                      hipStream_t st);
+// One minibatch step: the rows idx[0..batch) of X and T (an index outside [0, rows) reads as NaN),
+// loss and gradient, Adam step `step` (beta1 0.9, beta2 0.999, eps 1e-8); *loss (or nothing, nullptr) is written.
+hipError_t mlp_train_step(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, float *P, float *M, float *V,
+                          int64_t step, const float *X, int64_t ldx, const float *T, int64_t ldt, int rows,
+                          const int32_t *idx, int batch, double lr, double *loss, char *ws, size_t ws_bytes,
+                          hipStream_t st);
 
 // Warm start (warm.hip).  Features of every row of S (n x HAP_WARM_FEATURES floats) with
 // scratch of warm_feature_scratch_bytes(n); training targets of the current state; warm

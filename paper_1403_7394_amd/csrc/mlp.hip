@@ -6,6 +6,7 @@
 // W1 (n_in x hidden, row-major), b1, W2 (hidden x hidden), b2, W3 (hidden x n_out), b3.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "hap_internal.h"
@@ -172,19 +173,486 @@ __global__ __launch_bounds__(256) void colsum_rows_kernel(const float *__restric
 
 // Adam (Kingma and Ba, 2015): m and v are the first and second moment estimates, bc1 and bc2
 // the bias corrections 1 - beta^step.
+struct AdamArgs {
+    float b1, omb1, b2, omb2, lr, eps, bc1, bc2;
+};
+__device__ __forceinline__ void adam_update(float &p, float &mv, float &vv, float g, const AdamArgs &ad) {
+#pragma clang fp contract(off)
+    const float m = ad.b1 * mv + ad.omb1 * g;
+    const float v = ad.b2 * vv + ad.omb2 * (g * g);
+    mv = m;
+    vv = v;
+    p = p - ad.lr * (m / ad.bc1) / (sqrtf(v / ad.bc2) + ad.eps);
+}
 __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ P, const float *__restrict__ G,
                                                    float *__restrict__ Mv, float *__restrict__ Vv, int64_t count,
-                                                   float b1, float omb1, float b2, float omb2, float lr, float eps,
-                                                   float bc1, float bc2) {
-#pragma clang fp contract(off)
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) {
-        const float g = G[i];
-        const float m = b1 * Mv[i] + omb1 * g;
-        const float v = b2 * Vv[i] + omb2 * (g * g);
-        Mv[i] = m;
-        Vv[i] = v;
-        P[i] = P[i] - lr * (m / bc1) / (sqrtf(v / bc2) + eps);
+                                                   AdamArgs ad) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256)
+        adam_update(P[i], Mv[i], Vv[i], G[i], ad);
+}
+
+// ---------------------------------------------------------------------------
+// The whole perceptron in one or two launches (n_in <= 32, hidden <= 256, n_out <= 16; the warm
+// start's is 32 -> 128 -> 128 -> L).
+//
+// mlp_tile_kernel: a workgroup takes tiles of 32 rows; wave w owns hidden columns
+// [32 w, 32 w + 32) of both hidden layers, so everything between two layers passes through LDS
+// and only X and Y touch memory.  TRAIN: the backward pass of the tile too, and what the
+// parameter gradients contract over the rows goes to memory once, in the order in which the MFMA
+// of the gradient reads it (one 16 x 32-row fragment is 64 consecutive lane vectors).
+// mlp_grad_kernel: a wave per 16 x 16 tile of a weight gradient runs one chain of MFMAs over all
+// rows and applies the Adam step to its parameters.
+//
+// Every product is the one mlp_gemm_kernel forms (the same MFMA, k ascending from a zero
+// accumulator, the same epilogue) and the bias gradients add in colsum_rows_kernel's order, so the
+// results are those of the layer-by-layer path bit for bit.  That path spends a step of
+// 32 -> 128 -> 128 -> 3 at 4096 rows (1.96 ms) in its weight gradients: a 128 x 128 product over
+// 4096 rows is four 64 x 64 tiles, four workgroups that each wait for 128 loads in turn.  The
+// chain itself (128 MFMAs of 8 passes) takes 2 us; both kernels here are bound by latency.  Measured
+// in BF16: that step 1.96 ms -> 39 us (tiles 26 us, gradients and Adam 14 us), the prediction of 65536
+// rows 99 -> 18 us (layer by layer H1 and H2 travel through memory, 134 MB).
+// ---------------------------------------------------------------------------
+constexpr int kTile = 32;   // rows of a tile: one k step of the BF16 MFMA
+
+template <bool BF16> struct Mx;
+template <> struct Mx<true> {
+    typedef __bf16 E;
+    typedef bf16x8 F;
+    static constexpr int KS = 32, PAD = 8;
+    static __device__ __forceinline__ E cvt(float x) { return rne_bf16(x); }
+    static __device__ __forceinline__ F ld(const E *row, int k0, int kg) { return *(const F *)(row + k0 + 8 * kg); }
+    static __device__ __forceinline__ f32x4 mma(F a, F b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
     }
+    // elements k of p[k * stride], zero from K >= 1 on and where !ok (loads from valid addresses and
+    // selects: a branch per element costs more than the load)
+    static __device__ __forceinline__ F global(const float *p, int stride, int k0, int kg, int K, bool ok) {
+        float v[8];
+        F f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = p[min(k0 + 8 * kg + e, K - 1) * stride];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] = rne_bf16(ok && k0 + 8 * kg + e < K ? v[e] : 0.f);
+        return f;
+    }
+    // rows 16 rb + 4 kg + r (r = 0..3) of unit u = lane % 16 into the tile's fragment, in which
+    // lane 16 (row / 8) + u holds rows 8 (row / 8) .. + 7
+    static __device__ __forceinline__ void put(E *frag, int rb, int kg, int u, f32x4 v) {
+        typedef E E4 __attribute__((ext_vector_type(4)));
+        E4 o;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = rne_bf16(v[r]);
+        *(E4 *)(frag + ((2 * rb + (kg >> 1)) * 16 + u) * 8 + 4 * (kg & 1)) = o;
+    }
+    static __device__ __forceinline__ void put1(E *frag, int row, int u, float v) {
+        frag[((row >> 3) * 16 + u) * 8 + (row & 7)] = rne_bf16(v);
+    }
+};
+template <> struct Mx<false> {
+    typedef float E;
+    typedef float F;
+    static constexpr int KS = 4, PAD = 4;
+    static __device__ __forceinline__ E cvt(float x) { return x; }
+    static __device__ __forceinline__ F ld(const E *row, int k0, int kg) { return row[k0 + kg]; }
+    static __device__ __forceinline__ f32x4 mma(F a, F b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ F global(const float *p, int stride, int k0, int kg, int K, bool ok) {
+        const int k = k0 + kg;
+        return ok && k < K ? p[k * stride] : 0.f;
+    }
+    // fragment of k step q (rows 4 q .. 4 q + 3): lane 16 (row % 4) + u holds row 4 q + row % 4
+    static __device__ __forceinline__ void put(E *frag, int rb, int kg, int u, f32x4 v) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) frag[(4 * rb + kg) * 64 + r * 16 + u] = v[r];
+    }
+    static __device__ __forceinline__ void put1(E *frag, int row, int u, float v) {
+        frag[(row >> 2) * 64 + (row & 3) * 16 + u] = v;
+    }
+};
+
+constexpr int kFuseIn = 32, kFuseOut = 16, kFuseHidden = 256;
+constexpr int kFrag = 16 * kTile;   // elements of one block of 16 units over one tile
+
+// Where the training kernels keep a batch's operands in the workspace (bytes).  Fragments:
+// [block of 16 units][tile][kFrag] of X, H1, H2, dY, dH1, dH2; the unrounded dH1, dH2 and dY for the
+// bias gradients: [unit][row]; one squared-error sum per tile.
+struct FuseLayout {
+    int tiles, bh;         // tiles of rows; blocks of hidden units
+    int64_t rows;          // tiles * kTile
+    size_t X, H1, H2, dY, d1, d2, f1, f2, fy, loss, bytes;
+};
+FuseLayout fuse_layout(int hidden, int n_out, int64_t rows, bool bf16) {
+    FuseLayout f{};
+    f.tiles = (int)((rows + kTile - 1) / kTile);
+    f.rows = (int64_t)f.tiles * kTile;
+    f.bh = (hidden + 15) / 16;
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+        const size_t o = off;
+        off += (bytes + 255) & ~(size_t)255;
+        return o;
+    };
+    const size_t frag = (size_t)f.tiles * kFrag * (bf16 ? 2 : 4);
+    f.X = take(frag * (kFuseIn / 16));
+    f.H1 = take(frag * f.bh);
+    f.H2 = take(frag * f.bh);
+    f.dY = take(frag);
+    f.d1 = take(frag * f.bh);
+    f.d2 = take(frag * f.bh);
+    f.f1 = take((size_t)f.rows * hidden * 4);
+    f.f2 = take((size_t)f.rows * hidden * 4);
+    f.fy = take((size_t)f.rows * n_out * 4);
+    f.loss = take((size_t)f.tiles * 8);
+    f.bytes = off;
+    return f;
+}
+
+struct FuseArgs {
+    const float *P;          // parameters
+    MlpLayout lo;
+    int n_in, H, n_out;
+    const float *X;
+    int64_t ldx;
+    const int32_t *idx;      // rows of X and T to take (nullptr: 0, 1, ...); outside [0, x_rows): NaN
+    int x_rows;
+    int rows, tiles;
+    float *Y;                // forward
+    int64_t ldy;
+    const float *T;          // TRAIN
+    int64_t ldt;
+    float scale;             // 2 / (rows n_out)
+    FuseLayout fl;
+    char *ws;
+};
+
+template <bool BF16, int HP, bool TRAIN>
+__global__ __launch_bounds__(2 * HP) void mlp_tile_kernel(FuseArgs g) {
+    using M = Mx<BF16>;
+    using E = typename M::E;
+    using F = typename M::F;
+    constexpr int RT = kTile, RB = RT / 16, NT = 2 * HP;
+    constexpr int KS = M::KS, PAD = M::PAD;
+    constexpr int NKH = HP / KS, NKI = kFuseIn / KS;              // k steps over hidden units, inputs
+    constexpr int KO = BF16 ? 32 : 16, NKO = KO / KS;             // over outputs (zero past 16)
+    __shared__ __attribute__((aligned(16))) E Xs[RT][kFuseIn + PAD];
+    __shared__ __attribute__((aligned(16))) E H1s[RT][HP + PAD];
+    __shared__ __attribute__((aligned(16))) E H2s[RT][HP + PAD];  // TRAIN: then dH2
+    __shared__ __attribute__((aligned(16))) E dYs[TRAIN ? RT : 1][TRAIN ? KO + PAD : 1];
+    __shared__ double redl[RB];
+
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int r16 = lane & 15, kg = lane >> 4;
+    const int H = g.H, n_in = g.n_in, n_out = g.n_out;
+    const float *W1 = g.P + g.lo.oW1, *W2 = g.P + g.lo.oW2, *W3 = g.P + g.lo.oW3;
+    // this lane's column of each of the wave's two blocks of hidden units (clamped for addresses)
+    int col[2], colc[2];
+    float bias1[2], bias2[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        col[c] = wid * 32 + 16 * c + r16;
+        colc[c] = col[c] < H ? col[c] : H - 1;
+        bias1[c] = col[c] < H ? g.P[g.lo.ob1 + col[c]] : 0.f;
+        bias2[c] = col[c] < H ? g.P[g.lo.ob2 + col[c]] : 0.f;
+    }
+    const float bias3 = r16 < n_out ? g.P[g.lo.ob3 + r16] : 0.f;
+    const int outc = r16 < n_out ? r16 : n_out - 1;
+    // Weight fragments: in registers over the tiles (they are the same for every tile), except
+    // where they do not fit (training at 256 units), which reads them where they are used.
+    constexpr bool KEEP = HP <= 128 || !TRAIN;
+    auto read_w2 = [&](int k, int c) { return M::global(W2 + colc[c], H, k * KS, kg, H, col[c] < H); };
+    auto read_w2t = [&](int k, int c) {
+        return M::global(W2 + colc[c] * H, 1, k * KS, kg, H, col[c] < H);
+    };
+    auto read_w3 = [&](int k) { return M::global(W3 + outc, n_out, k * KS, kg, H, r16 < n_out); };
+    F w1[NKI][2], w2[KEEP ? NKH : 1][2], w3[KEEP ? NKH : 1];
+    F w2t[TRAIN && KEEP ? NKH : 1][2], w3t[TRAIN ? NKO : 1][2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int k = 0; k < NKI; ++k) w1[k][c] = M::global(W1 + colc[c], H, k * KS, kg, n_in, col[c] < H);
+    if constexpr (KEEP) {
+#pragma unroll
+        for (int k = 0; k < NKH; ++k) {
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                w2[k][c] = read_w2(k, c);
+                if constexpr (TRAIN) w2t[k][c] = read_w2t(k, c);
+            }
+            if (wid < RB) w3[k] = read_w3(k);
+        }
+    }
+    if constexpr (TRAIN) {
+#pragma unroll
+        for (int k = 0; k < NKO; ++k)
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                w3t[k][c] = M::global(W3 + colc[c] * n_out, 1, k * KS, kg, n_out, col[c] < H);
+        // outputs 16.. of the dY tile stay zero
+        if constexpr (KO > kFuseOut)
+            for (int e = tid; e < RT * (KO - kFuseOut); e += NT)
+                dYs[e / (KO - kFuseOut)][kFuseOut + e % (KO - kFuseOut)] = M::cvt(0.f);
+    }
+    const f32x4 z4 = (f32x4){0.f, 0.f, 0.f, 0.f};
+
+    for (int tile = blockIdx.x; tile < g.tiles; tile += gridDim.x) {
+        const int64_t row0 = (int64_t)tile * RT;
+        // a tile's fragment of block b of an operand
+        auto frag = [&](size_t region, int b) { return (E *)(g.ws + region) + ((int64_t)b * g.tiles + tile) * kFrag; };
+        for (int e = tid; e < RT * kFuseIn; e += NT) {
+            const int r = e / kFuseIn, k = e % kFuseIn;
+            const int64_t row = row0 + r;
+            float v = 0.f;
+            if (row < g.rows && k < n_in) {
+                const int64_t src = g.idx ? g.idx[row] : row;
+                v = (src >= 0 && src < g.x_rows) ? g.X[src * g.ldx + k] : __builtin_nanf("");
+            }
+            Xs[r][k] = M::cvt(v);
+            if constexpr (TRAIN) M::put1(frag(g.fl.X, k >> 4), r, k & 15, v);
+        }
+        __syncthreads();
+        // hidden layers; rows past the end hold zero from layer 1 on, so they add nothing below
+        unsigned on1 = 0, on2 = 0;   // bit 8 rb + 4 c + r: unit active at that row
+        f32x4 acc[RB][2];
+        auto clear = [&]() {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) acc[rb][c] = z4;
+        };
+        auto activate = [&](E(*hs)[HP + PAD], size_t region, const float(&bias)[2], unsigned &on) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    f32x4 h;
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int m = 16 * rb + 4 * kg + r;
+                        float v = acc[rb][c][r] + bias[c];
+                        v = v > 0.f ? v : 0.f;
+                        if (row0 + m >= g.rows) v = 0.f;
+                        on |= (v > 0.f ? 1u : 0u) << (8 * rb + 4 * c + r);
+                        h[r] = v;
+                        hs[m][col[c]] = M::cvt(v);
+                    }
+                    if constexpr (TRAIN) {
+                        if (wid * 2 + c < g.fl.bh) M::put(frag(region, wid * 2 + c), rb, kg, r16, h);
+                    }
+                }
+        };
+        // acc += hs x (the wave's columns of a hidden x hidden weight), k ascending
+        auto over_hidden = [&](const E(*hs)[HP + PAD], const F(*kept)[2], auto &&read) {
+            auto step = [&](int k, const F(&b)[2]) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) {
+                    const F a = M::ld(hs[16 * rb + r16], k * KS, kg);
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) acc[rb][c] = M::mma(a, b[c], acc[rb][c]);
+                }
+            };
+            if constexpr (KEEP) {
+#pragma unroll
+                for (int k = 0; k < NKH; ++k) step(k, kept[k]);
+            } else {
+#pragma unroll(BF16 ? 1 : 8)
+                for (int k = 0; k < NKH; ++k) {
+                    const F b[2] = {read(k, 0), read(k, 1)};
+                    step(k, b);
+                }
+            }
+        };
+        clear();
+#pragma unroll
+        for (int k = 0; k < NKI; ++k)
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    acc[rb][c] = M::mma(M::ld(Xs[16 * rb + r16], k * KS, kg), w1[k][c], acc[rb][c]);
+        activate(H1s, g.fl.H1, bias1, on1);
+        __syncthreads();
+        clear();
+        over_hidden(H1s, w2, read_w2);
+        activate(H2s, g.fl.H2, bias2, on2);
+        __syncthreads();
+        // outputs: wave w < RB holds rows 16 w .. 16 w + 15
+        if (wid < RB) {
+            f32x4 y = z4;
+            if constexpr (KEEP) {
+#pragma unroll
+                for (int k = 0; k < NKH; ++k) y = M::mma(M::ld(H2s[16 * wid + r16], k * KS, kg), w3[k], y);
+            } else {
+#pragma unroll(BF16 ? 1 : 8)
+                for (int k = 0; k < NKH; ++k) y = M::mma(M::ld(H2s[16 * wid + r16], k * KS, kg), read_w3(k), y);
+            }
+            f32x4 dy = z4;
+            double lsum = 0.0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = 16 * wid + 4 * kg + r;
+                const int64_t row = row0 + m;
+                const float v = y[r] + bias3;
+                const bool in = row < g.rows && r16 < n_out;
+                if constexpr (!TRAIN) {
+                    if (in) g.Y[row * g.ldy + r16] = v;
+                } else {
+                    if (in) {
+                        const int64_t src = g.idx ? g.idx[row] : row;
+                        const float t = (src >= 0 && src < g.x_rows) ? g.T[src * g.ldt + r16] : __builtin_nanf("");
+                        const float d = v - t;
+                        dy[r] = g.scale * d;
+                        lsum += (double)d * (double)d;
+                    }
+                    dYs[m][r16] = M::cvt(dy[r]);
+                }
+            }
+            if constexpr (TRAIN) {
+                M::put(frag(g.fl.dY, 0), wid, kg, r16, dy);
+                if (r16 < n_out)
+                    *(f32x4 *)((float *)(g.ws + g.fl.fy) + r16 * g.fl.rows + row0 + 16 * wid + 4 * kg) = dy;
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
+                if (lane == 0) redl[wid] = lsum;
+            }
+        }
+        if constexpr (TRAIN) {
+            __syncthreads();
+            if (tid == 0) ((double *)(g.ws + g.fl.loss))[tile] = redl[0] + redl[1];
+            // masks acc where the unit was off and hands it on
+            auto masked = [&](unsigned on, size_t region, size_t plain, bool keep) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) {
+                        f32x4 v;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            v[r] = (on >> (8 * rb + 4 * c + r)) & 1u ? acc[rb][c][r] : 0.f;
+                            if (keep) H2s[16 * rb + 4 * kg + r][col[c]] = M::cvt(v[r]);
+                        }
+                        if (wid * 2 + c < g.fl.bh) M::put(frag(region, wid * 2 + c), rb, kg, r16, v);
+                        if (col[c] < H)
+                            *(f32x4 *)((float *)(g.ws + plain) + col[c] * g.fl.rows + row0 + 16 * rb + 4 * kg) = v;
+                    }
+            };
+            // dH2 = (dY W3^T) where H2 > 0, dH1 = (dH2 W2^T) where H1 > 0
+            clear();
+#pragma unroll
+            for (int k = 0; k < NKO; ++k)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                    for (int c = 0; c < 2; ++c)
+                        acc[rb][c] = M::mma(M::ld(dYs[16 * rb + r16], k * KS, kg), w3t[k][c], acc[rb][c]);
+            masked(on2, g.fl.d2, g.fl.f2, true);
+            __syncthreads();
+            clear();
+            over_hidden(H2s, w2t, read_w2t);
+            masked(on1, g.fl.d1, g.fl.f1, false);
+        }
+        __syncthreads();
+    }
+}
+
+struct GradArgs {
+    MlpLayout lo;
+    FuseLayout fl;
+    const char *ws;
+    int n_in, H, n_out, rows;
+    double *loss;             // or nullptr
+    float *G;                 // gradient (no ADAM)
+    float *P, *Mv, *Vv;       // ADAM
+    AdamArgs ad;
+};
+
+// Parameter gradients from a batch's operands.  Workgroups, in order: one per 16 x 16 tile of
+// gW2, gW1, gW3 (one wave, one accumulator, rows ascending; the loads of 16 tiles of rows are in flight
+// together), one per bias (256 threads, colsum_rows_kernel's sum), one for the loss.
+template <bool BF16, bool ADAM>
+__global__ __launch_bounds__(256) void mlp_grad_kernel(GradArgs g) {
+    using M = Mx<BF16>;
+    using E = typename M::E;
+    using F = typename M::F;
+    constexpr int PER = BF16 ? 1 : 8;        // MFMA steps per tile of rows
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int bh = g.fl.bh, bi = (g.n_in + 15) / 16;
+    auto emit = [&](int64_t i, float v) {
+        if constexpr (ADAM)
+            adam_update(g.P[i], g.Mv[i], g.Vv[i], v, g.ad);
+        else
+            g.G[i] = v;
+    };
+    int b = blockIdx.x;
+    const int n2 = bh * bh, n1 = bi * bh, n3 = bh;
+    if (b < n2 + n1 + n3) {
+        if (wid > 0) return;
+        size_t ra, rb;
+        int ba, bb, M_, N_;
+        int64_t out;
+        if (b < n2) {
+            ra = g.fl.H1, rb = g.fl.d2, ba = b / bh, bb = b % bh, M_ = g.H, N_ = g.H, out = g.lo.oW2;
+        } else if (b < n2 + n1) {
+            b -= n2;
+            ra = g.fl.X, rb = g.fl.d1, ba = b / bh, bb = b % bh, M_ = g.n_in, N_ = g.H, out = g.lo.oW1;
+        } else {
+            ra = g.fl.H2, rb = g.fl.dY, ba = b - n2 - n1, bb = 0, M_ = g.H, N_ = g.n_out, out = g.lo.oW3;
+        }
+        const F *A = (const F *)((const E *)(g.ws + ra) + (int64_t)ba * g.fl.tiles * kFrag) + lane;
+        const F *B = (const F *)((const E *)(g.ws + rb) + (int64_t)bb * g.fl.tiles * kFrag) + lane;
+        f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
+        constexpr int UN = BF16 ? 16 : 2;    // tiles of rows in flight
+        int t = 0;
+        for (; t + UN <= g.fl.tiles; t += UN) {
+            F fa[UN * PER], fb[UN * PER];
+#pragma unroll
+            for (int k = 0; k < UN * PER; ++k) {
+                fa[k] = A[((int64_t)t * PER + k) * 64];
+                fb[k] = B[((int64_t)t * PER + k) * 64];
+            }
+#pragma unroll
+            for (int k = 0; k < UN * PER; ++k) acc = M::mma(fa[k], fb[k], acc);
+        }
+        for (; t < g.fl.tiles; ++t)
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                acc = M::mma(A[((int64_t)t * PER + k) * 64], B[((int64_t)t * PER + k) * 64], acc);
+        const int n = 16 * bb + (lane & 15);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = 16 * ba + 4 * (lane >> 4) + r;
+            if (m < M_ && n < N_) emit(out + (int64_t)m * N_ + n, acc[r]);
+        }
+        return;
+    }
+    b -= n2 + n1 + n3;
+    if (b < 2 * g.H + g.n_out) {
+        // bias gradient: the sum of one unit's row of f1, f2 or fy
+        __shared__ float part[4];
+        const size_t region = b < g.H ? g.fl.f1 : b < 2 * g.H ? g.fl.f2 : g.fl.fy;
+        const int u = b < g.H ? b : b < 2 * g.H ? b - g.H : b - 2 * g.H;
+        const float *x = (const float *)(g.ws + region) + u * g.fl.rows;
+        float acc = 0.f;
+#pragma unroll 8
+        for (int r = tid; r < g.rows; r += 256) acc += x[r];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+        if (lane == 0) part[wid] = acc;
+        __syncthreads();
+        if (tid == 0)
+            emit((b < g.H ? g.lo.ob1 : b < 2 * g.H ? g.lo.ob2 : g.lo.ob3) + u,
+                 (part[0] + part[1]) + (part[2] + part[3]));
+        return;
+    }
+    // loss: the tiles' squared errors, in a fixed order
+    __shared__ double lp[4];
+    double s = 0.0;
+    for (int t = tid; t < g.fl.tiles; t += 256) s += ((const double *)(g.ws + g.fl.loss))[t];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) lp[wid] = s;
+    __syncthreads();
+    if (tid == 0 && g.loss) *g.loss = ((lp[0] + lp[1]) + (lp[2] + lp[3])) / ((double)g.rows * g.n_out);
 }
 
 // Rows idx[0..rows) of X (width w, row stride ldx, x_rows rows) into a packed buffer; an
@@ -237,6 +705,80 @@ GemmArgs make_gemm(const float *A, int64_t sam, int64_t sak, const float *B, int
         if (_e != hipSuccess) return _e;     \
     } while (0)
 
+// Networks small enough for the fused kernels (register and LDS budgets set the limits).
+bool fuse_ok(int n_in, int hidden, int n_out) {
+    return n_in <= kFuseIn && hidden <= kFuseHidden && n_out <= kFuseOut;
+}
+
+// At most 1024 workgroups (about four per CU of the 256): past that a workgroup takes several
+// tiles and reads the weights once for all of them.
+template <bool BF16, int HP, bool TRAIN>
+hipError_t launch_tile(const FuseArgs &g, hipStream_t st) {
+    const int grid = g.tiles < 1024 ? g.tiles : 1024;
+    hipLaunchKernelGGL((mlp_tile_kernel<BF16, HP, TRAIN>), dim3(grid), dim3(2 * HP), 0, st, g);
+    return hipGetLastError();
+}
+
+template <bool TRAIN>
+hipError_t run_tiles(bool bf16, const FuseArgs &g, hipStream_t st) {
+    if (g.H <= 64) return bf16 ? launch_tile<true, 64, TRAIN>(g, st) : launch_tile<false, 64, TRAIN>(g, st);
+    if (g.H <= 128) return bf16 ? launch_tile<true, 128, TRAIN>(g, st) : launch_tile<false, 128, TRAIN>(g, st);
+    return bf16 ? launch_tile<true, 256, TRAIN>(g, st) : launch_tile<false, 256, TRAIN>(g, st);
+}
+
+FuseArgs fuse_args(const MlpLayout &lo, int n_in, int hidden, int n_out, const float *P, const float *X, int64_t ldx,
+                   int rows) {
+    FuseArgs g{};
+    g.P = P;
+    g.lo = lo;
+    g.n_in = n_in;
+    g.H = hidden;
+    g.n_out = n_out;
+    g.X = X;
+    g.ldx = ldx;
+    g.x_rows = rows;
+    g.rows = rows;
+    g.tiles = (int)(((int64_t)rows + kTile - 1) / kTile);
+    return g;
+}
+
+// Loss and gradient (G), or loss and Adam step (P, Mv, Vv) of `rows` rows, idx[r] of X and T if idx.
+template <bool ADAM>
+hipError_t run_train(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, const float *P, const float *X,
+                     int64_t ldx, const float *T, int64_t ldt, const int32_t *idx, int rows, int x_rows, double *loss,
+                     float *G, float *Pw, float *Mv, float *Vv, const AdamArgs &ad, char *ws, hipStream_t st) {
+    FuseArgs g = fuse_args(lo, n_in, hidden, n_out, P, X, ldx, rows);
+    g.idx = idx;
+    g.x_rows = x_rows;
+    g.T = T;
+    g.ldt = ldt;
+    g.scale = (float)(2.0 / ((double)rows * n_out));
+    g.fl = fuse_layout(hidden, n_out, rows, bf16);
+    g.ws = ws;
+    MLP_TRY(run_tiles<true>(bf16, g, st));
+    GradArgs a{};
+    a.lo = lo;
+    a.fl = g.fl;
+    a.ws = ws;
+    a.n_in = n_in;
+    a.H = hidden;
+    a.n_out = n_out;
+    a.rows = rows;
+    a.loss = loss;
+    a.G = G;
+    a.P = Pw;
+    a.Mv = Mv;
+    a.Vv = Vv;
+    a.ad = ad;
+    const int bh = g.fl.bh;
+    const int grid = bh * bh + (n_in + 15) / 16 * bh + bh + 2 * hidden + n_out + 1;
+    if (bf16)
+        hipLaunchKernelGGL((mlp_grad_kernel<true, ADAM>), dim3(grid), dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL((mlp_grad_kernel<false, ADAM>), dim3(grid), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 MlpLayout mlp_layout(int n_in, int hidden, int n_out, int64_t rows) {
@@ -269,8 +811,18 @@ MlpLayout mlp_layout(int n_in, int hidden, int n_out, int64_t rows) {
     return lo;
 }
 
-hipError_t mlp_forward(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, const float *P,
-                       const float *X, int64_t ldx, int rows, float *Y, int64_t ldy, char *ws, hipStream_t st) {
+size_t mlp_workspace_bytes(int n_in, int hidden, int n_out, int64_t rows) {
+    size_t b = mlp_layout(n_in, hidden, n_out, rows).bytes;
+    if (fuse_ok(n_in, hidden, n_out))
+        for (const bool bf16 : {false, true}) b = std::max(b, fuse_layout(hidden, n_out, rows, bf16).bytes);
+    return b;
+}
+
+namespace {
+
+// Layer by layer; leaves H1 and H2 in the workspace for the backward pass.
+hipError_t layered_forward(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, const float *P,
+                           const float *X, int64_t ldx, int rows, float *Y, int64_t ldy, char *ws, hipStream_t st) {
     float *H1 = (float *)(ws + lo.H1), *H2 = (float *)(ws + lo.H2);
     const int H = hidden;
     MLP_TRY(gemm(bf16, make_gemm(X, ldx, 1, P + lo.oW1, H, 1, H1, H, rows, H, n_in, EPI_BIAS_RELU, P + lo.ob1), st));
@@ -279,13 +831,38 @@ hipError_t mlp_forward(const MlpLayout &lo, int n_in, int hidden, int n_out, boo
     return hipSuccess;
 }
 
+}  // namespace
+
+hipError_t mlp_forward(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, const float *P,
+                       const float *X, int64_t ldx, int rows, float *Y, int64_t ldy, char *ws, hipStream_t st) {
+    if (rows <= 0) return hipSuccess;
+    if (!fuse_ok(n_in, hidden, n_out))
+        return layered_forward(lo, n_in, hidden, n_out, bf16, P, X, ldx, rows, Y, ldy, ws, st);
+    FuseArgs g = fuse_args(lo, n_in, hidden, n_out, P, X, ldx, rows);
+    g.Y = Y;
+    g.ldy = ldy;
+    return run_tiles<false>(bf16, g, st);
+}
+
+namespace {
+
+AdamArgs adam_args(int64_t step, double lr, double b1, double b2, double eps) {
+    const double bc1 = 1.0 - std::pow(b1, (double)step), bc2 = 1.0 - std::pow(b2, (double)step);
+    return {(float)b1, (float)(1.0 - b1), (float)b2, (float)(1.0 - b2), (float)lr, (float)eps, (float)bc1, (float)bc2};
+}
+
+}  // namespace
+
 hipError_t mlp_loss_grad(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, const float *P,
                          const float *X, int64_t ldx, const float *T, int64_t ldt, int rows, float *G, double *loss,
-                         char *ws, hipStream_t st) {
+                         char *ws, size_t ws_bytes, hipStream_t st) {
     const int H = hidden;
+    if (fuse_ok(n_in, hidden, n_out) && ws_bytes >= fuse_layout(hidden, n_out, rows, bf16).bytes)
+        return run_train<false>(lo, n_in, hidden, n_out, bf16, P, X, ldx, T, ldt, nullptr, rows, rows, loss, G, nullptr,
+                                nullptr, nullptr, AdamArgs{}, ws, st);
     float *H1 = (float *)(ws + lo.H1), *H2 = (float *)(ws + lo.H2), *Y = (float *)(ws + lo.Y);
     float *dY = (float *)(ws + lo.dY), *dH2 = (float *)(ws + lo.dH2), *dH1 = (float *)(ws + lo.dH1);
-    MLP_TRY(mlp_forward(lo, n_in, hidden, n_out, bf16, P, X, ldx, rows, Y, n_out, ws, st));
+    MLP_TRY(layered_forward(lo, n_in, hidden, n_out, bf16, P, X, ldx, rows, Y, n_out, ws, st));
     hipLaunchKernelGGL(mse_kernel, dim3(1), dim3(1024), 0, st, Y, (int64_t)n_out, T, ldt, rows, n_out, dY, loss);
     MLP_TRY(hipGetLastError());
     // layer 3: gW3 = H2^T dY, gb3 = column sums of dY, dH2 = (dY W3^T) masked by H2 > 0
@@ -307,13 +884,13 @@ hipError_t mlp_loss_grad(const MlpLayout &lo, int n_in, int hidden, int n_out, b
 
 hipError_t mlp_adam(float *P, const float *G, float *M, float *V, int64_t count, int64_t step, double lr, double b1,
                     double b2, double eps, hipStream_t st) {
-    const double bc1 = 1.0 - std::pow(b1, (double)step), bc2 = 1.0 - std::pow(b2, (double)step);
     const int64_t blocks = (count + 255) / 256;
     const int grid = (int)(blocks < 4096 ? blocks : 4096);
-    hipLaunchKernelGGL(adam_kernel, dim3(grid), dim3(256), 0, st, P, G, M, V, count, (float)b1, (float)(1.0 - b1),
-                       (float)b2, (float)(1.0 - b2), (float)lr, (float)eps, (float)bc1, (float)bc2);
+    hipLaunchKernelGGL(adam_kernel, dim3(grid), dim3(256), 0, st, P, G, M, V, count, adam_args(step, lr, b1, b2, eps));
     return hipGetLastError();
 }
+
+namespace {
 
 hipError_t mlp_gather(const float *X, int64_t ldx, int w, const int32_t *idx, int rows, int x_rows, float *out,
                       hipStream_t st) {
@@ -322,6 +899,24 @@ hipError_t mlp_gather(const float *X, int64_t ldx, int w, const int32_t *idx, in
     hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, X, ldx, w, idx,
                        rows, x_rows, out);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t mlp_train_step(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, float *P, float *M, float *V,
+                          int64_t step, const float *X, int64_t ldx, const float *T, int64_t ldt, int rows,
+                          const int32_t *idx, int batch, double lr, double *loss, char *ws, size_t ws_bytes,
+                          hipStream_t st) {
+    float *G = (float *)(ws + lo.G);
+    if (fuse_ok(n_in, hidden, n_out) && ws_bytes >= fuse_layout(hidden, n_out, batch, bf16).bytes)
+        return run_train<true>(lo, n_in, hidden, n_out, bf16, P, X, ldx, T, ldt, idx, batch, rows, loss, nullptr, P, M, V,
+                               adam_args(step, lr, 0.9, 0.999, 1e-8), ws, st);
+    float *Xb = (float *)(ws + lo.Xb), *Tb = (float *)(ws + lo.Tb);
+    MLP_TRY(mlp_gather(X, ldx, n_in, idx, batch, rows, Xb, st));
+    MLP_TRY(mlp_gather(T, ldt, n_out, idx, batch, rows, Tb, st));
+    MLP_TRY(mlp_loss_grad(lo, n_in, hidden, n_out, bf16, P, Xb, n_in, Tb, n_out, batch, G,
+                          loss ? loss : (double *)(ws + lo.loss), ws, 0, st));
+    return mlp_adam(P, G, M, V, lo.count, step, lr, 0.9, 0.999, 1e-8, st);
 }
 
 }  // namespace hap
