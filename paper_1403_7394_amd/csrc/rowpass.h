@@ -159,6 +159,28 @@ __device__ __forceinline__ void wave_reduce(T &m1, int &k1, T &m2, T &cv, int &c
     if constexpr (WITH_C) ck = __builtin_amdgcn_readlane(ck, 63);
 }
 
+// Buffer-resource accesses (raw buffer instructions): a per-row resource, the lane's byte
+// offset in a VGPR and the chunk offset as a scalar, so a chunk costs no address registers.
+// Loads past the resource's range return 0 and stores past it are dropped.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void *p, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes, 0x00020000);
+}
+template <typename V, int AUX>
+__device__ __forceinline__ V buf_load(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
+    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, AUX));
+}
+// Stores take the chunk offset in the VGPR offset and a constant zero scalar offset: a store of
+// more than 64 bits reads its data registers after issue, and the compiler keeps a VALU write
+// of those registers one wait state away from the store only when the scalar offset is not a
+// register.  With an SGPR offset a write scheduled right behind the store has corrupted the
+// stored values of some lanes.
+template <typename V, int AUX>
+__device__ __forceinline__ void buf_store(V v, __amdgpu_buffer_rsrc_t r, int voff, int soff) {
+    typedef unsigned int U4 __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), r, voff + soff, 0, AUX);
+}
+constexpr int kNT = 2;  // cache-policy operand: non-temporal
+
 // Rows whose per-row scalars are staged in LDS at a time.
 constexpr int kWin = 64;
 
@@ -562,5 +584,10 @@ __device__ __forceinline__ void sweep_rows_points(const SweepArgs<T> &a, const i
     }
     if (chg) atomicOr(&a.ds->changed, 1);
 }
+
+// The row pass with several rows of a workgroup in flight (flowpass.h): threads per row 64, 128, 256 or
+// 512, four chunks per thread, nb workgroups of a.rb rows (2..kWin).
+template <typename T, int D>
+hipError_t launch_flow(const SweepArgs<T> &a, int threads, int nb, bool tail, hipStream_t st);
 
 }  // namespace hap

@@ -93,28 +93,6 @@ __global__ __launch_bounds__(NT) void sweep_kernel(SweepArgs<T> a) {
     }
 }
 
-// Buffer-resource accesses (raw buffer instructions): a per-row resource, the lane's byte
-// offset in a VGPR and the chunk offset as a scalar, so a chunk costs no address registers.
-// Loads past the resource's range return 0 and stores past it are dropped.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void *p, int64_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)0, (int)bytes, 0x00020000);
-}
-template <typename V, int AUX>
-__device__ __forceinline__ V buf_load(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-    return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, AUX));
-}
-// Stores take the chunk offset in the VGPR offset and a constant zero scalar offset: a store of
-// more than 64 bits reads its data registers after issue, and the compiler keeps a VALU write
-// of those registers one wait state away from the store only when the scalar offset is not a
-// register.  With an SGPR offset a write scheduled right behind the store has corrupted the
-// stored values of some lanes.
-template <typename V, int AUX>
-__device__ __forceinline__ void buf_store(V v, __amdgpu_buffer_rsrc_t r, int voff, int soff) {
-    typedef unsigned int U4 __attribute__((ext_vector_type(4)));
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(U4, v), r, voff + soff, 0, AUX);
-}
-constexpr int kNT = 2;  // cache-policy operand: non-temporal
-
 // Row pass for rows too long to keep in registers (large N, 1024 threads).  Same arithmetic
 // as sweep_rows.  The chunks of a row are visited by a runtime loop: phase 1 streams S, R,
 // A and B; phase 2 reads the row's S and R again (normal loads, so the second read is
@@ -1097,6 +1075,18 @@ hipError_t launch_resident(const SweepArgs<T> &a, const Launch &lc, int nb, bool
     return hipGetLastError();
 }
 
+// The row pass with several rows of a workgroup in flight (flowpass.h): FP32, four chunks per thread and
+// from two to kWin rows per workgroup (their scalars are staged once).  Against the one-row pass, per
+// level with its column sums: 788 points 19.8 -> 11.6 us, 2000 points 35.8 -> 20.6, 3000 points 53.2 ->
+// 36.8, 6000 points 148 -> 136, in points mode 57 -> 34 (3000) and 135 -> 115 (6000).  Rows of 8192
+// columns that read S are bound by memory either way and stay with the one-row pass, whose
+// prefetched row covers the latency without LDS traffic (240 us against 246); so do FP64 rows (4000
+// points 125 us against 130).
+bool flow_fits(const Launch &lc, size_t elem, bool reads_s, bool tail) {
+    return elem == 4 && !lc.streaming && lc.chunks == 4 && lc.threads <= 512 && lc.rows_per_block > 1 &&
+           lc.rows_per_block <= kWin && (tail || lc.threads < 512 || !reads_s);
+}
+
 template <typename T>
 hipError_t launch_sweep_level(const T *S, int64_t lds, const LevelPtrs<T> &lv, T *phi_down,
                               const T *tau_l, int n, int64_t ldw, double lam, T *Qpart, const Launch &lc,
@@ -1177,7 +1167,17 @@ hipError_t launch_sweep_level(const T *S, int64_t lds, const LevelPtrs<T> &lv, T
             hipLaunchKernelGGL((sweep_stream_kernel<T, 1024, false>), dim3(nb), dim3(1024), 0, st, a, lc.chunks);
         return hipGetLastError();
     }
-    if (ex.delta != nullptr) return launch_resident<T, -1>(a, lc, nb, tail, st);   // reads S (no points mode)
+    // with Eq. 2.7 offsets the pass reads S (no points mode)
+    const bool reads_s = ex.delta != nullptr || X == nullptr;
+    if constexpr (sizeof(T) == 4) {
+        if (flow_fits(lc, sizeof(T), reads_s, tail)) {
+            if (ex.delta != nullptr) return launch_flow<T, -1>(a, lc.threads, nb, tail, st);
+            if (X == nullptr) return launch_flow<T, 0>(a, lc.threads, nb, tail, st);
+            if (d == 2) return launch_flow<T, 2>(a, lc.threads, nb, tail, st);
+            if (d == 3) return launch_flow<T, 3>(a, lc.threads, nb, tail, st);
+        }
+    }
+    if (ex.delta != nullptr) return launch_resident<T, -1>(a, lc, nb, tail, st);
     if (X == nullptr) return launch_resident<T, 0>(a, lc, nb, tail, st);
     if constexpr (sizeof(T) == 4) {
         if (d == 2) return launch_resident<T, 2>(a, lc, nb, tail, st);
