@@ -47,6 +47,8 @@ struct Launch {
     bool ordered;       // column partials summed strictly in workgroup order
     bool streaming;     // large rows: 1024 threads, phase 2 re-reads S and R (chunks 2..16); or, FP32
                         // with 512 threads x 16 chunks, the held-row pass (phase 2 reads nothing)
+    bool held = false;  // the default for FP32 rows of 8192 < n <= 16384: reported as the streaming shape,
+                        // run by the held-row pass (the same bits)
     bool blocks = false; // workgroup g takes rows [g rb, (g + 1) rb) instead of g, g + G, g + 2G, ...
                          // (G workgroups), the default, under which the rows in flight at any
                          // moment are neighbours in memory
@@ -159,6 +161,9 @@ struct FusedArgs {
 };
 bool fused_supported(int threads, int chunks, int levels);
 hipError_t launch_sweep_fused(const FusedArgs<float> &a, const Launch &lc, hipStream_t st);
+// Its form with several rows of a workgroup in flight (64, 128 or 256 threads per row, 2..64 rows per
+// workgroup).
+hipError_t launch_fused_flow(const FusedArgs<float> &a, int threads, int nb, bool tail, hipStream_t st);
 template <typename T>
 hipError_t launch_alpha_pad(T *A, int64_t rows, int n, int64_t ldw, hipStream_t st);
 

@@ -52,3 +52,49 @@ def test_equals_the_streaming_pass(hap_gpu, n, threads, rb, form):
     for x, y in zip(a, b):
         for k in x:
             assert torch.equal(torch.nan_to_num(x[k], nan=7e30), torch.nan_to_num(y[k], nan=7e30)), (form, k)
+
+
+@pytest.mark.parametrize("n,threads,rb", [s for s in SHAPES if s[1] < 512])
+@pytest.mark.parametrize("levels", [2, 4])
+def test_fused_levels_equal_the_per_level_passes(hap_gpu, n, threads, rb, levels):
+    """The MapReduce schedule's all-level pass with several rows in flight."""
+    hap = hap_gpu
+    rng = np.random.default_rng([n, rb, levels])
+    X = torch.from_numpy((rng.standard_normal((n, 2)) * 3 + 20 * rng.integers(0, 4, (n, 1))).astype(np.float32)).to(DEV)
+    S = torch.empty((n, (n + 3) // 4 * 4), dtype=torch.float32, device=DEV)[:, :n]
+    hap.build_similarity(X, S)
+    got = []
+    for unfused in (False, True):
+        h = hap.Hap(S, levels, 0.6, schedule=hap.SCHEDULE_MRHAP)
+        h.set_launch(*((threads, 4, rb) if not unfused else (1024, (n + 4095) // 4096, rb)), streaming=unfused,
+                     unfused=unfused)
+        assert bool(h.launch_flags() & hap.LAUNCH_FUSED) == (not unfused)
+        h.iterate(5)
+        got.append([h.messages(level) for level in range(levels)] + [dict(labels=h.labels())])
+        h.close()
+    for x, y in zip(*got):
+        for k in x:
+            assert torch.equal(x[k], y[k]), k
+
+
+@pytest.mark.parametrize("n", [8193, 12288, 12289, 16384])
+def test_held_rows_of_six_and_eight_chunks(hap_gpu, n):
+    """The default pass of FP32 rows of 8192 < n <= 16384 against the streaming shape it reports."""
+    hap = hap_gpu
+    rng = np.random.default_rng(n)
+    X = torch.from_numpy(rng.standard_normal((n, 2)).astype(np.float32) * 10).to(DEV)
+    S = torch.empty((n, (n + 3) // 4 * 4), dtype=torch.float32, device=DEV)[:, :n]
+    hap.build_similarity(X, S)
+    got = []
+    for explicit in (False, True):
+        h = hap.Hap(S, 2, 0.7)
+        shape = h.get_launch()
+        assert shape == (1024, (n + 4095) // 4096, (n + 255) // 256, True)
+        if explicit:
+            h.set_launch(*shape[:3], streaming=True)
+        h.iterate(3)
+        got.append([h.messages(level) for level in range(2)] + [dict(labels=h.labels())])
+        h.close()
+    for x, y in zip(*got):
+        for k in x:
+            assert torch.equal(x[k], y[k]), k
