@@ -216,6 +216,7 @@ Launch default_launch(int64_t n, size_t esz) {
             lc.threads = 0;
             return lc;
         }
+        lc.held = esz == 4 && n <= 512 * 8 * 4;
     }
     // About 256 workgroups (one per CU) on large problems.  Small problems (FP32 up to 512
     // points, FP64 up to 2048) take one row per workgroup and sum the column partials in
@@ -1052,6 +1053,7 @@ hap_status hap_set_launch(hap_ctx *c, int32_t threads, int32_t chunks, int32_t r
     if (threads) lc.threads = threads;
     if (chunks) lc.chunks = chunks;
     if (rows_per_block) lc.rows_per_block = rows_per_block;
+    if (threads || chunks || flags >= 0) lc.held = false;   // the shape asked for
     if (flags >= 0) lc.streaming = (flags & HAP_LAUNCH_STREAM) != 0;
     if (flags >= 0) lc.blocks = (flags & HAP_LAUNCH_BLOCKS) != 0;
     lc.ordered = (lc.rows_per_block == 1);

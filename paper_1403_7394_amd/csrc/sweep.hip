@@ -1147,10 +1147,21 @@ hipError_t launch_sweep_level(const T *S, int64_t lds, const LevelPtrs<T> &lv, T
         }
         return hipErrorInvalidValue;
     }
-    if (lc.streaming && lc.threads == 512) {
-        // the held-row pass: FP32, 512 threads x 16 chunks (n <= 32768)
+    if (lc.streaming && (lc.threads == 512 || lc.held)) {
+        // the held-row pass: FP32, 512 threads x 16 chunks (n <= 32768), of which rows of up to 16384
+        // columns need only eight (and, of up to 12288, six): with the column sums, 10609 points
+        // take 443 us a level (5.1 TB/s), 495 us streamed; 16384 points 988 and 1087
         if constexpr (sizeof(T) == 4) {
-            if (lc.chunks != 16 || n > 512 * 16 * 4) return hipErrorInvalidValue;
+            if ((lc.threads == 512 && lc.chunks != 16) || n > 512 * 16 * 4) return hipErrorInvalidValue;
+            if (n <= 512 * 6 * 4) {
+                hipLaunchKernelGGL((sweep_held_kernel<512, 6, true>), dim3(nb), dim3(512), 0, st, a);
+                return hipGetLastError();
+            }
+            if (n <= 512 * 8 * 4) {
+                hipLaunchKernelGGL((sweep_held_kernel<512, 8, true>), dim3(nb), dim3(512), 0, st, a);
+                return hipGetLastError();
+            }
+            const bool tail = n != 512 * 16 * 4;
             if (tail)
                 hipLaunchKernelGGL((sweep_held_kernel<512, 16, true>), dim3(nb), dim3(512), 0, st, a);
             else
