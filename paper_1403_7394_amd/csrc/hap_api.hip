@@ -389,8 +389,9 @@ hap_status run_sweeps(hap_ctx *c, int count, int K) {
                 fa.lam = (float)c->lam;
                 fa.oml = (float)(1.0 - c->lam);
                 fa.ds = c->ds;
+                LevelPtrs<float> fl[hap::kMaxFused];
                 for (int l = 0; l < L; ++l) {
-                    LevelPtrs<float> lv = level_ptrs<float>(c, l);
+                    const LevelPtrs<float> lv = fl[l] = level_ptrs<float>(c, l);
                     fa.R[l] = lv.R;
                     fa.A[l] = lv.A;
                     fa.pref[l] = lv.pref;
@@ -405,9 +406,14 @@ hap_status run_sweeps(hap_ctx *c, int count, int K) {
                 HIP_TRY(prof_mark(c, 0, false), c);
                 HIP_TRY(hap::launch_sweep_fused(fa, c->lc, c->stream), c);
                 HIP_TRY(prof_mark(c, 0, true), c);
-                for (int l = 0; l < L; ++l) {
-                    const hap_status s = col(l, (T *)fa.Qpart[l], false);
-                    if (s != HAP_OK) return s;
+                if (c->lc.ordered || c->prof) {
+                    // one launch per level, which hap_profile counts
+                    for (int l = 0; l < L; ++l) {
+                        const hap_status s = col(l, (T *)fa.Qpart[l], false);
+                        if (s != HAP_OK) return s;
+                    }
+                } else {
+                    HIP_TRY(hap::launch_colsum_levels(fa, fl, nb, K, c->stream), c);
                 }
                 continue;
             }

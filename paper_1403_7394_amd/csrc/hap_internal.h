@@ -164,6 +164,9 @@ hipError_t launch_sweep_fused(const FusedArgs<float> &a, const Launch &lc, hipSt
 // Its form with several rows of a workgroup in flight (64, 128 or 256 threads per row, 2..64 rows per
 // workgroup).
 hipError_t launch_fused_flow(const FusedArgs<float> &a, int threads, int nb, bool tail, hipStream_t st);
+// Column sums, availability bases and stop rule of every level after the fused pass (unordered partials,
+// nb per level).
+hipError_t launch_colsum_levels(const FusedArgs<float> &f, const LevelPtrs<float> *lv, int nb, int K, hipStream_t st);
 template <typename T>
 hipError_t launch_alpha_pad(T *A, int64_t rows, int n, int64_t ldw, hipStream_t st);
 

@@ -821,76 +821,147 @@ struct ColArgs {
     T *B_top;            // B^l = Q^l at the top level, else nullptr
     T *B_down;           // B^{l-1}, nullptr at l = 0
     const T *C_down, *phi_down, *Q_down;
+    T *B_own;            // B^l = (c^l + phi^l) + Q^l, where phi^l is there already (the fused pass), or nullptr
+    const T *phi_own;
+    int skip_done;       // after an early stop the partials are stale: keep the sums
     int last, K;
     DevState *ds;
 };
 
-template <typename T, int NG>
-__global__ __launch_bounds__(16 * NG) void colsum_kernel(ColArgs<T> a) {
+constexpr int kColVecs = 16;   // column vectors per workgroup (256-byte segments of the partial rows; four, for
+                               // more workgroups, take 4.7 us against 4.5 at 788 points, 5.9 against 5.2 at 8192)
+
+// What follows a column sum: elements j0 .. of Q^l and of the vectors formed from it.  V is a vector or a
+// scalar of T; cv = c^l and bd = B^{l-1} of these columns were loaded before the sum.
+template <typename T, typename V>
+__device__ __forceinline__ void col_before(const ColArgs<T> &a, int j0, V &cv, V &bd, V &ph) {
 #pragma clang fp contract(off)
-    using V = typename Vec<T>::type;
-    constexpr int VW = Vec<T>::N;
-    __shared__ V sh[NG][16];
-    // After an early stop the row passes do nothing and the shared partial buffer is stale, so
-    // the levels below the top keep their sums.  The top level's partials are the last ones
-    // written, so its launch (which also applies the stop rule, and is the only one that can
-    // set the flag) recomputes the same values.
-    if (!a.last && a.ds->done) return;
-    // 16 column vectors per workgroup; group g sums partial rows g, g+NG, g+2NG, ... in order
-    const int col = threadIdx.x & 15, g = threadIdx.x >> 4;
-    const int j0 = (blockIdx.x * 16 + col) * VW;
-    const int n = a.n, nb = a.nb;
-    // the vectors the sums are combined with were written before this launch: load them first,
-    // so that their latency overlaps that of the partials
-    V cv = (V)(T(0)), bd = (V)(T(0));
-    if (g == 0 && j0 < n) {
-        if (a.tau_next != nullptr) cv = *(const V *)(a.C + j0);
-        if (a.B_down != nullptr)
-            bd = (*(const V *)(a.C_down + j0) + *(const V *)(a.phi_down + j0)) + *(const V *)(a.Q_down + j0);
-    }
-    V acc = (V)(T(0));
-    if (j0 < n) {
-        if (NG == 1) {
-            // strictly sequential adds; the loads are issued 16 ahead
-#pragma unroll 16
-            for (int b = 0; b < nb; ++b) acc += *(const V *)(a.Qpart + (int64_t)b * a.ldw + j0);
-        } else {
-#pragma unroll 4
-            for (int b = g; b < nb; b += NG) acc += *(const V *)(a.Qpart + (int64_t)b * a.ldw + j0);
+    if (a.tau_next != nullptr || a.B_own != nullptr) cv = *(const V *)(a.C + j0);
+    if (a.B_own != nullptr) ph = *(const V *)(a.phi_own + j0);
+    if (a.B_down != nullptr)
+        bd = (*(const V *)(a.C_down + j0) + *(const V *)(a.phi_down + j0)) + *(const V *)(a.Q_down + j0);
+}
+template <typename T, typename V>
+__device__ __forceinline__ void col_after(const ColArgs<T> &a, int j0, V tot, V cv, V bd, V ph) {
+#pragma clang fp contract(off)
+    *(V *)(a.Q + j0) = tot;
+    if (a.tau_next != nullptr) *(V *)(a.tau_next + j0) = cv + tot;
+    if (a.B_top != nullptr) *(V *)(a.B_top + j0) = tot;
+    if (a.B_own != nullptr) *(V *)(a.B_own + j0) = (cv + ph) + tot;
+    if (a.B_down != nullptr) *(V *)(a.B_down + j0) = bd;
+}
+// Iteration counter and stop rule (one thread of the top level's launch).
+template <typename T>
+__device__ __forceinline__ void col_stop_rule(const ColArgs<T> &a) {
+    DevState *ds = a.ds;
+    if (ds->done) return;
+    const int tcur = ds->t + 1;
+    if (tcur >= 2) {
+        const int it = tcur - 1;  // label iteration compared during this sweep
+        if (it >= 2 && !ds->changed)
+            ds->stable += 1;
+        else
+            ds->stable = 0;
+        if (a.K > 0 && ds->stable >= a.K) {
+            ds->done = 1;
+            ds->stop_iter = it;
         }
     }
-    if (NG > 1) {
-        sh[g][col] = acc;
-        __syncthreads();
+    ds->changed = 0;
+    ds->t = tcur;
+}
+
+// After an early stop the row passes do nothing and a partial buffer shared by the levels is
+// stale, so the levels below the top keep their sums (skip_done).  The top level's partials are
+// the last ones written, so its launch (which also applies the stop rule, and is the only one that
+// can set the flag) recomputes the same values.
+//
+// 64 groups of kColVecs column vectors per workgroup: group g sums partial rows g, g + 64, ... in order, then
+// the groups' sums are added in order.  Latency-bound (a load, LDS, 63 adds), so the
+// partials are loaded before anything is known of the state.
+template <typename T>
+__device__ __forceinline__ void colsum_body(const ColArgs<T> &a) {
+#pragma clang fp contract(off)
+    using V = typename Vec<T>::type;
+    constexpr int VW = Vec<T>::N, NG = 64, CV = kColVecs;
+    __shared__ V sh[NG][CV];
+    const int col = threadIdx.x % CV, g = threadIdx.x / CV;
+    const int j0 = (blockIdx.x * CV + col) * VW;
+    const int n = a.n, nb = a.nb;
+    V acc = (V)(T(0));
+    if (j0 < n) {
+#pragma unroll 4
+        for (int b = g; b < nb; b += NG) acc += *(const V *)(a.Qpart + (int64_t)b * a.ldw + j0);
     }
+    V cv = (V)(T(0)), bd = (V)(T(0)), ph = (V)(T(0));
+    if (g == 0 && j0 < n) col_before(a, j0, cv, bd, ph);
+    const bool skip = a.skip_done && a.ds->done;
+    sh[g][col] = acc;
+    __syncthreads();
+    if (skip) return;
     if (g == 0 && j0 < n) {
         V tot = acc;
 #pragma unroll
         for (int k = 1; k < NG; ++k) tot += sh[k][col];
-        *(V *)(a.Q + j0) = tot;
-        if (a.tau_next != nullptr) *(V *)(a.tau_next + j0) = cv + tot;
-        if (a.B_top != nullptr) *(V *)(a.B_top + j0) = tot;
-        if (a.B_down != nullptr) *(V *)(a.B_down + j0) = bd;
+        col_after(a, j0, tot, cv, bd, ph);
     }
-    if (a.last && blockIdx.x == 0 && threadIdx.x == 0) {
-        DevState *ds = a.ds;
-        if (!ds->done) {
-            const int tcur = ds->t + 1;
-            if (tcur >= 2) {
-                const int it = tcur - 1;  // label iteration compared during this sweep
-                if (it >= 2 && !ds->changed)
-                    ds->stable += 1;
-                else
-                    ds->stable = 0;
-                if (a.K > 0 && ds->stable >= a.K) {
-                    ds->done = 1;
-                    ds->stop_iter = it;
-                }
-            }
-            ds->changed = 0;
-            ds->t = tcur;
+    if (a.last && blockIdx.x == 0 && threadIdx.x == 0) col_stop_rule(a);
+}
+
+template <typename T>
+__global__ __launch_bounds__(64 * kColVecs) void colsum_kernel(ColArgs<T> a) {
+    colsum_body<T>(a);
+}
+
+// Every level's column sums in one launch (the fused pass, whose levels have their own partials).
+struct ColLevels {
+    ColArgs<float> level[kMaxFused];
+};
+__global__ __launch_bounds__(64 * kColVecs) void colsum_levels_kernel(ColLevels a) {
+    colsum_body<float>(a.level[blockIdx.y]);
+}
+
+// Strictly in workgroup order (one row per workgroup: row order, the order of a plain sequential
+// sum).  Sixteen columns per workgroup: 256 threads bring 256 partial rows at a time into LDS, the
+// next 256 on their way to registers meanwhile, and sixteen threads add them one after another.  (One
+// thread per column vector that loads sixteen rows ahead waits a memory latency per sixteen rows: 12.0
+// us at 300 FP64 points against 5.0 us.)
+template <typename T>
+__global__ __launch_bounds__(256) void colsum_ordered_kernel(ColArgs<T> a) {
+#pragma clang fp contract(off)
+    constexpr int CB = 16, RT = 256, PER = RT / 16;
+    __shared__ T tile[2][RT][CB];
+    const int tid = threadIdx.x, c = tid & 15, r = tid >> 4;
+    const int j = blockIdx.x * CB + c;
+    const int n = a.n, nb = a.nb;
+    const T *src = a.Qpart + (j < n ? j : n - 1);
+    T x[PER];
+    auto load = [&](int b0) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int b = b0 + r + 16 * k;
+            x[k] = src[(int64_t)(b < nb ? b : nb - 1) * a.ldw];
+        }
+    };
+    load(0);
+    T cv = T(0), bd = T(0), ph = T(0), acc = T(0);
+    if (tid < CB && j < n) col_before(a, j, cv, bd, ph);
+    const bool skip = a.skip_done && a.ds->done;
+    int buf = 0;
+    for (int b0 = 0; b0 < nb; b0 += RT, buf ^= 1) {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) tile[buf][r + 16 * k][c] = x[k];
+        __syncthreads();
+        if (b0 + RT < nb) load(b0 + RT);
+        if (tid < CB) {
+            const int m = nb - b0 < RT ? nb - b0 : RT;
+#pragma unroll 16
+            for (int k = 0; k < m; ++k) acc += tile[buf][k][c];
         }
     }
+    if (skip) return;
+    if (tid < CB && j < n) col_after(a, j, acc, cv, bd, ph);
+    if (a.last && blockIdx.x == 0 && tid == 0) col_stop_rule(a);
 }
 
 // alpha^{l,t} materialised on the fly from A = alpha^{t-1}, R = rho^t (nothing in the
@@ -1197,32 +1268,63 @@ hipError_t launch_sweep_level(const T *S, int64_t lds, const LevelPtrs<T> &lv, T
     return hipErrorInvalidValue;
 }
 
+namespace {
+
 template <typename T>
-hipError_t launch_colsum(const T *Qpart, int64_t ldw, int nb, int n, const LevelPtrs<T> &lv,
-                         const LevelPtrs<T> *down, T *tau_next, bool top, bool last, int K, bool ordered,
-                         DevState *ds, hipStream_t st) {
-    constexpr int VW = Vec<T>::N;
-    ColArgs<T> a;
+ColArgs<T> col_args(const T *Qpart, int64_t ldw, int nb, int n, const LevelPtrs<T> &lv, bool top, bool last, int K,
+                    DevState *ds) {
+    ColArgs<T> a{};
     a.Qpart = Qpart;
     a.ldw = ldw;
     a.nb = nb;
     a.n = n;
     a.Q = lv.Q;
     a.C = lv.C;
-    a.tau_next = tau_next;
     a.B_top = top ? lv.B : nullptr;
+    a.skip_done = last ? 0 : 1;
+    a.last = last ? 1 : 0;
+    a.K = K;
+    a.ds = ds;
+    return a;
+}
+
+}  // namespace
+
+template <typename T>
+hipError_t launch_colsum(const T *Qpart, int64_t ldw, int nb, int n, const LevelPtrs<T> &lv,
+                         const LevelPtrs<T> *down, T *tau_next, bool top, bool last, int K, bool ordered,
+                         DevState *ds, hipStream_t st) {
+    constexpr int VW = Vec<T>::N;
+    ColArgs<T> a = col_args<T>(Qpart, ldw, nb, n, lv, top, last, K, ds);
+    a.tau_next = tau_next;
     a.B_down = down ? down->B : nullptr;
     a.C_down = down ? down->C : nullptr;
     a.phi_down = down ? down->phi : nullptr;
     a.Q_down = down ? down->Q : nullptr;
-    a.last = last ? 1 : 0;
-    a.K = K;
-    a.ds = ds;
-    const int blocks = (n + 16 * VW - 1) / (16 * VW);
+    auto blocks = [&](int per) { return dim3((unsigned)((n + per - 1) / per)); };
     if (ordered)
-        hipLaunchKernelGGL((colsum_kernel<T, 1>), dim3(blocks), dim3(16), 0, st, a);
+        hipLaunchKernelGGL((colsum_ordered_kernel<T>), blocks(16), dim3(256), 0, st, a);
     else
-        hipLaunchKernelGGL((colsum_kernel<T, 64>), dim3(blocks), dim3(16 * 64), 0, st, a);
+        hipLaunchKernelGGL((colsum_kernel<T>), blocks(kColVecs * VW), dim3(64 * kColVecs), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_colsum_levels(const FusedArgs<float> &f, const LevelPtrs<float> *lv, int nb, int K, hipStream_t st) {
+    ColLevels c{};
+    for (int l = 0; l < f.L; ++l) {
+        const bool top = l == f.L - 1;
+        ColArgs<float> &a = c.level[l];
+        a = col_args<float>(f.Qpart[l], f.ldw, nb, f.n, lv[l], top, top, K, f.ds);
+        // every level has its own partials: after an early stop they give the same sums again
+        a.skip_done = 0;
+        if (!top) {
+            // phi^l was written by this launch's row pass
+            a.B_own = lv[l].B;
+            a.phi_own = lv[l].phi;
+        }
+    }
+    const dim3 grid((unsigned)((f.n + kColVecs * 4 - 1) / (kColVecs * 4)), (unsigned)f.L);
+    hipLaunchKernelGGL(colsum_levels_kernel, grid, dim3(64 * kColVecs), 0, st, c);
     return hipGetLastError();
 }
 
