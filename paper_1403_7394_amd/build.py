@@ -19,7 +19,7 @@ LIB = os.path.join(PKG, "libhap.so")
 ARCH = "gfx950"
 
 SOURCES = ["hap_api.hip", "sweep.hip", "select.hip", "misc.hip", "build.hip", "batch.hip", "warm.hip", "mlp.hip", "levelsim.hip", "fused.hip",
-           "flow.hip", "flow_points.hip", "flow_fused.hip"]
+           "flow.hip", "flow_points.hip", "flow_fused.hip", "row1.hip"]
 
 
 def hipcc() -> str:

@@ -57,6 +57,7 @@ __device__ __forceinline__ void lds_wait(const int *p, int at_least) {
 
 // Second maximum after y joins (m1 the maximum before): a y that compares with nothing (NaN) is ignored.
 __device__ __forceinline__ float second_max(float m1, float m2, float y) { return __builtin_amdgcn_fmed3f(m1, m2, y); }
+__device__ __forceinline__ double second_max(double m1, double m2, double y) { return y > m1 ? m1 : fmax(m2, y); }
 
 // Two (max, second max) pairs: the smaller maximum competes for second place.
 template <typename T>
@@ -91,6 +92,12 @@ __device__ __forceinline__ void flow_reduce(T &m1, T &m2, T &cv, int &ck) {
     flow_step<T, WITH_C, 0x143, 0xc>(m1, m2, cv, ck);   // row_bcast:31 into rows 2, 3
 }
 __device__ __forceinline__ float lane63(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63)); }
+__device__ __forceinline__ double lane63(double v) {
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(x & 0xffffffffll), 63);
+    const int hi = __builtin_amdgcn_readlane((int)(x >> 32), 63);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
 
 // One row of one level, as a group of NTG threads holds it: s and rho of the row, and in `a` alpha
 // (before) or alpha + s (after phase 1) of this thread's columns.

@@ -590,4 +590,8 @@ __device__ __forceinline__ void sweep_rows_points(const SweepArgs<T> &a, const i
 template <typename T, int D>
 hipError_t launch_flow(const SweepArgs<T> &a, int threads, int nb, bool tail, hipStream_t st);
 
+// The row pass with one row per workgroup (row1.hip): threads per row 64 to 512, four chunks per thread.
+template <typename T, int D>
+hipError_t launch_row1(const SweepArgs<T> &a, int threads, bool tail, hipStream_t st);
+
 }  // namespace hap

@@ -1259,6 +1259,14 @@ hipError_t launch_sweep_level(const T *S, int64_t lds, const LevelPtrs<T> &lv, T
             if (d == 3) return launch_flow<T, 3>(a, lc.threads, nb, tail, st);
         }
     }
+    if (lc.rows_per_block == 1 && lc.chunks == 4 && lc.threads <= 512) {
+        if (ex.delta != nullptr) return launch_row1<T, -1>(a, lc.threads, tail, st);
+        if (X == nullptr) return launch_row1<T, 0>(a, lc.threads, tail, st);
+        if constexpr (sizeof(T) == 4) {
+            if (d == 2) return launch_row1<T, 2>(a, lc.threads, tail, st);
+            if (d == 3) return launch_row1<T, 3>(a, lc.threads, tail, st);
+        }
+    }
     if (ex.delta != nullptr) return launch_resident<T, -1>(a, lc, nb, tail, st);
     if (X == nullptr) return launch_resident<T, 0>(a, lc, nb, tail, st);
     if constexpr (sizeof(T) == 4) {
