@@ -13,7 +13,7 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("dtype", [np.float64, np.float32])
-@pytest.mark.parametrize("n", [2, 15, 17, 255, 256, 257, 513])
+@pytest.mark.parametrize("n", [2, 15, 17, 255, 256, 257, 511, 512, 513, 1025])
 def test_row_ordered_sums_match_the_oracle(hap_gpu, n, dtype):
     rng = np.random.default_rng(n)
     X = (rng.standard_normal((n, 2)) * 2 + 15 * rng.integers(0, 3, (n, 1))).astype(dtype)
@@ -23,7 +23,7 @@ def test_row_ordered_sums_match_the_oracle(hap_gpu, n, dtype):
     Sh = S.cpu().numpy()
     p = dtype(-20.0)
     h = hap_gpu.Hap(S, 2, 0.6, pref=float(p))
-    assert h.get_launch()[2] == (1 if n <= 512 or dtype == np.float64 else 3)
+    assert h.get_launch()[2] == (1 if n <= 512 or dtype == np.float64 else (n + 255) // 256)
     h.set_launch(rows_per_block=1)
     h.iterate(5)
     ref = hap_ref.hap(Sh, np.full(n, p, dtype=dtype), 2, 0.6, 5, dtype=dtype)
