@@ -16,7 +16,7 @@
 // spin forever.
 #include <algorithm>
 
-#include "rowpass.h"
+#include "flowpass.h"
 
 namespace hap {
 
@@ -66,16 +66,26 @@ __device__ void build_instance(const float *__restrict__ X, int64_t d, int n, in
             for (int e = threadIdx.x; e < rows * d; e += NT) xs[e] = (double)X[(int64_t)(i0 + e / d) * d + e % d];
             __syncthreads();
             if (j < n) {
+                // eight rows at a time, so that a coordinate of the column is loaded once for eight of them
                 const float *xj = X + (int64_t)j * d;
-                for (int r = 0; r < rows; ++r) {
-                    double acc = 0.0;
+                for (int r = 0; r < rows; r += 8) {
+                    double acc[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) acc[u] = 0.0;
                     for (int k = 0; k < d; ++k) {
-                        const double df = xs[r * d + k] - (double)xj[k];
-                        const double sq = df * df;
-                        acc = acc + sq;
+                        const double xk = (double)xj[k];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const double df = xs[min(r + u, rows - 1) * d + k] - xk;
+                            const double sq = df * df;
+                            acc[u] = acc[u] + sq;
+                        }
                     }
-                    const int i = i0 + r;
-                    S[(int64_t)i * ld + j] = (i == j) ? 0.f : (float)(-acc);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int i = i0 + r + u;
+                        if (r + u < rows) S[(int64_t)i * ld + j] = (i == j) ? 0.f : (float)(-acc[u]);
+                    }
                 }
             }
         }
@@ -129,12 +139,13 @@ __device__ float median_instance(const float *__restrict__ S, int n, int ld, uns
         const int shift = hi - width;
         for (int b = threadIdx.x; b < kBins; b += NT) hist[b] = 0u;
         __syncthreads();
-        for (long long e = threadIdx.x; e < (long long)n * n; e += NT) {
-            const int i = (int)(e / n), j = (int)(e % n);
-            if (i == j) continue;
-            const unsigned int k = fkey(S[(int64_t)i * ld + j]);
-            if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & ((1u << width) - 1u)], 1u);
-        }
+        // a wave per row
+        for (int i = threadIdx.x >> 6; i < n; i += NT / 64)
+#pragma unroll 4
+            for (int j = threadIdx.x & 63; j < n; j += 64) {
+                const unsigned int k = fkey(S[(int64_t)i * ld + j]);
+                if (i != j && (k & mask) == prefix) atomicAdd(&hist[(k >> shift) & ((1u << width) - 1u)], 1u);
+            }
         __syncthreads();
         if (threadIdx.x == 0) {
             long long cum = 0;
@@ -164,12 +175,12 @@ __device__ float median_instance(const float *__restrict__ S, int n, int ld, uns
         if (threadIdx.x == 0) hist[0] = 0xFFFFFFFFu;
         __syncthreads();
         unsigned int best = 0xFFFFFFFFu;
-        for (long long e = threadIdx.x; e < (long long)n * n; e += NT) {
-            const int i = (int)(e / n), j = (int)(e % n);
-            if (i == j) continue;
-            const unsigned int k = fkey(S[(int64_t)i * ld + j]);
-            if (k > prefix && k < best) best = k;
-        }
+        for (int i = threadIdx.x >> 6; i < n; i += NT / 64)
+#pragma unroll 4
+            for (int j = threadIdx.x & 63; j < n; j += 64) {
+                const unsigned int k = fkey(S[(int64_t)i * ld + j]);
+                if (i != j && k > prefix && k < best) best = k;
+            }
         atomicMin(&hist[0], best);
         __syncthreads();
         hi_v = fval(hist[0]);
@@ -179,182 +190,133 @@ __device__ float median_instance(const float *__restrict__ S, int n, int ld, uns
 }
 
 
-// The rows of one instance in G row groups of NTG threads (NT = G * NTG): at step k group
-// g handles row row0 + k*G + g, so G rows are in flight per workgroup; every group takes
-// the same number of steps and barriers.  Per row the work is that of sweep_rows (Eq.
-// 2.1-2.6: finish alpha^{t-1}, reduce c/e and the top two of alpha + s, then rho^t).  The
-// column sums stay in row order: groups 1..G-1 publish their rows' contributions through
-// LDS and group 0 adds them, in row order, before it adds its own next row, so the sums
-// (in group 0's registers) are the sequential column sums.
+// The rows of one instance (or of one member's block) in G decoupled row groups of NTG threads, as in
+// flowpass.h: group g takes rows row0 + g, row0 + g + G, ...; the column sums are added in row order
+// through LDS, so they are the sequential column sums whatever the shape.
+// Measured at the default shape (512 threads, four groups) against groups that meet at a workgroup barrier
+// per step: 512 problems of 64..2048 points, 20 iterations, 280 -> 235 ms; 200 problems of 32..500
+// points, 40 iterations, 65 -> 22 ms; 256 of 32..200 points 17.0 -> 5.2 ms.
+// Its LDS is indexed by column vector and by wave, so it is the same for every cut into groups.
+constexpr int kBatchVecs = 512;     // column vectors of the longest row (2048 points)
+template <int NT>
+struct BatchLds {
+    Vec<float>::type q[kBatchVecs];   // column sums
+    float m1[2][NT / 64], m2[2][NT / 64], cv[2][NT / 64];
+    int ck[2][NT / 64];
+    int arrived[NT / 64];             // per group
+    int turn[NT / 64];                // per wave of a group
+};
+
 template <int NTG, int NCH, int G, bool FIRST>
-__device__ __forceinline__ void sweep_rows_grouped(const SweepArgs<float> &a, const int t, const int row0,
-                                                   const int row1, const float4v (&Bv)[NCH], float4v (&qv)[NCH],
-                                                   float (*sh_m1)[G][NTG / 64], int (*sh_k1)[G][NTG / 64],
-                                                   float (*sh_m2)[G][NTG / 64], float (*sh_cv)[G][NTG / 64],
-                                                   int (*sh_ck)[G][NTG / 64], float4v (*contrib)[G][NCH][G > 1 ? NTG : 1],
-                                                   int32_t *changed) {
+__device__ __forceinline__ void batch_rows(const SweepArgs<float> &a, const int t, const int row0, const int row1,
+                                           const Vec<float>::type (&Bv)[NCH], const float p, BatchLds<NTG * G> &L,
+                                           int32_t *changed) {
 #pragma clang fp contract(off)
-    constexpr int VW = 4;
-    constexpr int NWG = NTG / 64;
-    const int tid = threadIdx.x;
-    const int grp = tid / NTG, ltid = tid % NTG;
-    const int lane = tid & 63, wid = ltid >> 6;
+    using V = Vec<float>::type;
+    constexpr int VW = 4, NWG = NTG / 64, CB = NTG * 16;
+    const int grp = G > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NTG) : 0;
+    const int ltid = threadIdx.x % NTG, lane = ltid & 63, wid = __builtin_amdgcn_readfirstlane(ltid >> 6);
     const int n = a.n;
     const int64_t ldw = a.ldw;
-    const float lam = a.lam, oml = a.oml;
-    const float zero = 0.f, ninf = neg_inf<float>();
+    const int base = ltid * VW, voff = ltid * 16;
     const bool has_tau = a.tau != nullptr;
-    const int base = ltid * VW;
-    const int steps = (row1 - row0 + G - 1) / G;
-    int chg = 0;   // a label of this group's rows changed (the group's thread 0)
-    float4v xs[NCH], xr[NCH], xa[NCH];
-    for (int k = 0; k < steps; ++k) {
-        const int buf = k & 1;
-        const int i = row0 + k * G + grp;
-        const bool active = i < row1;
-        float m1 = ninf, m2 = ninf, cv = ninf;
-        int k1 = INT_MAX, ck = INT_MAX;
-        int dcol = i - base;
-        float p_i = 0.f, tau_i = 0.f;
-        int e_old = 0;
-        if (active) {
-            const float *Srow = a.S + (int64_t)i * a.lds;
-            const float *Rrow = a.R + (int64_t)i * ldw;
-            float *Arow = a.A + (int64_t)i * ldw;
-            // the row's scalars are loaded before its rows, so that waiting for them (memory
-            // operations complete in issue order) never waits for the row loads or for stores
-            p_i = a.pref[i];
-            if (has_tau) tau_i = a.tau[i];
-            if (!FIRST && ltid == 0) e_old = a.E[i];
+    const int64_t row_bytes = (int64_t)((n + VW - 1) / VW * VW) * 4;
+    int chg = 0, step = 0;
+    for (int i = row0 + grp; i < row1; i += G, ++step) {
+        const int buf = step & 1;
+        const __amdgpu_buffer_rsrc_t rS = row_rsrc(a.S + (int64_t)i * a.lds, row_bytes);
+        const __amdgpu_buffer_rsrc_t rR = row_rsrc(a.R + (int64_t)i * ldw, row_bytes);
+        const __amdgpu_buffer_rsrc_t rA = row_rsrc(a.A + (int64_t)i * ldw, row_bytes);
+        FlowRow<float, NTG, NCH> x;
+        // the row's scalars go out before the row, so that waiting for them is not waiting for it
+        const float tau_i = has_tau ? a.tau[i] : 0.f;
+        const int e_old = FIRST ? 0 : a.E[i];
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const int j0 = c * NTG * VW + base;
-                if (j0 < n) {
-                    xs[c] = __builtin_nontemporal_load((const float4v *)(Srow + j0));
-                    xr[c] = __builtin_nontemporal_load((const float4v *)(Rrow + j0));
-                    xa[c] = __builtin_nontemporal_load((const float4v *)(Arow + j0));
-                } else {
-                    xs[c] = (float4v)(0.f);
-                    xr[c] = (float4v)(0.f);
-                    xa[c] = (float4v)(ninf);
-                }
-            }
-            // phase 1: finish alpha^{t-1}, reduce c/e over alpha + rho and the top two of alpha + s
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const int j0 = c * NTG * VW + base;
-#pragma unroll
-                for (int v = 0; v < VW; ++v) {
-                    const int j = c * NTG * VW + v;
-                    const bool diag = dcol == j;
-                    const float sj = diag ? p_i : xs[c][v];
-                    xs[c][v] = sj;
-                    const float rj = xr[c][v];
-                    float al = xa[c][v];
-                    if constexpr (!FIRST) {
-                        const float Bj = Bv[c][v];
-                        const float ah = diag ? Bj - rj : fminf(zero, Bj - fmaxf(zero, rj));
-                        al = lam * al + oml * ah;
-                        xa[c][v] = al;
-                        const float cx = al + rj;
-                        const bool gsel = cx > cv;
-                        cv = gsel ? cx : cv;
-                        ck = gsel ? j : ck;
-                    }
-                    const float y = al + sj;
-                    const bool g1 = y > m1;
-                    m2 = g1 ? m1 : fmaxf(m2, y);
-                    k1 = g1 ? j : k1;
-                    m1 = g1 ? y : m1;
-                }
-                if constexpr (!FIRST) {
-                    if (j0 < n) __builtin_nontemporal_store(xa[c], (float4v *)(Arow + j0));
-                }
-            }
-            k1 = (k1 == INT_MAX) ? INT_MAX : k1 + base;
-            ck = (ck == INT_MAX) ? INT_MAX : ck + base;
-            wave_reduce<float, !FIRST>(m1, k1, m2, cv, ck);
-            if (lane == 0) {
-                sh_m1[buf][grp][wid] = m1;
-                sh_k1[buf][grp][wid] = k1;
-                sh_m2[buf][grp][wid] = m2;
-                if constexpr (!FIRST) {
-                    sh_cv[buf][grp][wid] = cv;
-                    sh_ck[buf][grp][wid] = ck;
-                }
-            }
+        for (int c = 0; c < NCH; ++c) {
+            x.s[c] = buf_load<V, kNT>(rS, voff, c * CB);
+            x.r[c] = buf_load<V, kNT>(rR, voff, c * CB);
+            x.a[c] = buf_load<V, kNT>(rA, voff, c * CB);
         }
-        // LDS exchange of the wave results and the contributions: wait for LDS traffic only,
-        // so that this step's stores stay in flight across the barrier
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0xc07f);
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        // group 0: the previous step's rows of groups 1..G-1, in row order, before its own row
-        if (grp == 0 && k > 0) {
-            const int pb = buf ^ 1;
-#pragma unroll
-            for (int gg = 1; gg < G; ++gg) {
-                if (row0 + (k - 1) * G + gg >= row1) break;
-#pragma unroll
-                for (int c = 0; c < NCH; ++c) qv[c] += contrib[pb][gg][c][ltid];
+        float m1, m2, cv;
+        int ck;
+        flow_phase1<float, NTG, NCH, FIRST, true, false>(
+            x, i, n, wid, base, a.lam, a.oml, p, 0.f, rA, voff, m1, m2, cv, ck, [&](int, V &) {},
+            [&](int c) { return Bv[c]; });
+        ck = (ck == INT_MAX) ? INT_MAX : ck + base;
+        flow_reduce<float, !FIRST>(m1, m2, cv, ck);
+        const int w0 = grp * NWG;   // the group's first wave
+        if constexpr (NWG > 1) {
+            if (lane == 63) {
+                L.m1[buf][w0 + wid] = m1;
+                L.m2[buf][w0 + wid] = m2;
+                L.cv[buf][w0 + wid] = cv;
+                L.ck[buf][w0 + wid] = ck;
             }
-        }
-        if (active) {
-            float *Rrow = a.R + (int64_t)i * ldw;
-            m1 = sh_m1[buf][grp][0];
-            k1 = sh_k1[buf][grp][0];
-            m2 = sh_m2[buf][grp][0];
+            lds_settle();
+            if (lane == 0) __hip_atomic_fetch_add(&L.arrived[grp], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            lds_wait(&L.arrived[grp], (step + 1) * NWG);
+            m1 = L.m1[buf][w0];
+            m2 = L.m2[buf][w0];
 #pragma unroll
-            for (int w = 1; w < NWG; ++w)
-                top2_merge(m1, k1, m2, sh_m1[buf][grp][w], sh_k1[buf][grp][w], sh_m2[buf][grp][w]);
+            for (int w = 1; w < NWG; ++w) pair_merge(m1, m2, L.m1[buf][w0 + w], L.m2[buf][w0 + w]);
+        } else {
+            m1 = lane63(m1);
+            m2 = lane63(m2);
+        }
+        if (ltid == 63) {
             if constexpr (!FIRST) {
-                if (ltid == 0) {
-                    cv = sh_cv[buf][grp][0];
-                    ck = sh_ck[buf][grp][0];
-                    for (int w = 1; w < NWG; ++w) argmax_merge(cv, ck, sh_cv[buf][grp][w], sh_ck[buf][grp][w]);
-                    a.C[i] = cv;
-                    if (a.phi_down) a.phi_down[i] = m1;
-                    a.E[i] = ck;
-                    chg |= (t >= 3 && e_old != ck) ? 1 : 0;
+                if constexpr (NWG > 1) {
+                    cv = L.cv[buf][w0];
+                    ck = L.ck[buf][w0];
+                    for (int w = 1; w < NWG; ++w) argmax_merge(cv, ck, L.cv[buf][w0 + w], L.ck[buf][w0 + w]);
                 }
+                a.C[i] = cv;
+                if (a.phi_down) a.phi_down[i] = m1;
+                a.E[i] = ck;
+                chg |= (t >= 3 && e_old != ck) ? 1 : 0;
             }
-            // phase 2: rho^t and this row's column-sum contribution
-            asm volatile("" : "+v"(dcol));
-            const int k1r = k1 - base;
+        }
+        flow_phase2<float, NTG, NCH, true>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fminf(tau_i, -m1) : -m1,
+                                           has_tau ? fminf(tau_i, -m2) : -m2, rR, voff);
+        if constexpr (G > 1) lds_wait(&L.turn[wid], i - row0);
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                const int j0 = c * NTG * VW + base;
-                float4v out, q;
+        for (int c = 0; c < NCH; ++c) {
+            if (c * NTG * VW + wid * 64 * VW >= n) continue;
+            V q = L.q[c * NTG + ltid];
 #pragma unroll
-                for (int v = 0; v < VW; ++v) {
-                    const int j = c * NTG * VW + v;
-                    const float m = (j == k1r) ? m2 : m1;
-                    const float rh = has_tau ? xs[c][v] + fminf(tau_i, -m) : xs[c][v] - m;
-                    const float rn = lam * xr[c][v] + oml * rh;
-                    out[v] = rn;
-                    q[v] = (dcol == j) ? rn : fmaxf(zero, rn);
-                }
-                if (grp == 0)
-                    qv[c] += q;
-                else
-                    contrib[buf][grp][c][ltid] = q;
-                if (j0 < n) __builtin_nontemporal_store(out, (float4v *)(Rrow + j0));
-            }
+            for (int v = 0; v < VW; ++v) q[v] += x.s[c][v];
+            L.q[c * NTG + ltid] = q;
+        }
+        if constexpr (G > 1) {
+            lds_settle();
+            if (lane == 0)
+                __hip_atomic_store(&L.turn[wid], i - row0 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
     }
     if (chg) atomicOr(changed, 1);
-    __syncthreads();
-    // the last step's rows of groups 1..G-1
-    if (grp == 0 && steps > 0) {
-        const int pb = (steps - 1) & 1;
+}
+
+// One level's rows: the bases, the rows, the column sums in L.q.
+template <int NTG, int NCH, int G>
+__device__ __forceinline__ void batch_level(const SweepArgs<float> &a, const int t, const int row0, const int row1,
+                                            const float p, BatchLds<NTG * G> &L, int32_t *changed) {
+    using V = Vec<float>::type;
+    constexpr int NT = NTG * G;
+    const int tid = threadIdx.x, ltid = tid % NTG;
+    V Bv[NCH];
 #pragma unroll
-        for (int gg = 1; gg < G; ++gg) {
-            if (row0 + (steps - 1) * G + gg >= row1) break;
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) qv[c] += contrib[pb][gg][c][ltid];
-        }
+    for (int c = 0; c < NCH; ++c) {
+        const int j0 = (c * NTG + ltid) * 4;
+        Bv[c] = (t > 1 && j0 < a.n) ? *(const V *)(a.B + j0) : (V)(0.f);
     }
+    for (int v = tid; v < kBatchVecs; v += NT) L.q[v] = (V)(0.f);
+    if (tid < NT / 64) L.arrived[tid] = L.turn[tid] = 0;
+    __syncthreads();
+    if (t == 1)
+        batch_rows<NTG, NCH, G, true>(a, t, row0, row1, Bv, p, L, changed);
+    else
+        batch_rows<NTG, NCH, G, false>(a, t, row0, row1, Bv, p, L, changed);
+    __syncthreads();   // c^l, phi^{l-1}, labels of this workgroup's rows are written
 }
 
 template <int NT, int G, int CH>
@@ -364,19 +326,14 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs g) {
     constexpr int VW = 4;
     constexpr int NW = NT / 64;
     constexpr int NTG = NT / G;          // threads per row group
-    __shared__ float sh_cv[2][NW];
-    __shared__ int sh_ck[2][NW];
-    __shared__ float gm1[2][G][NTG / 64], gm2[2][G][NTG / 64], gcv[2][G][NTG / 64];
-    __shared__ int gk1[2][G][NTG / 64], gck[2][G][NTG / 64];
-    __shared__ float4v contrib[2][G][CH][G > 1 ? NTG : 1];
+    __shared__ __attribute__((aligned(16))) BatchLds<NT> L;
     __shared__ unsigned int hist[kBins];
     __shared__ double xs[64 * 32];
     __shared__ int sh[4];
     __shared__ int sh_ok;
     __shared__ double shd[NW];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    const int ltid = tid % NTG;
-    const int L = g.levels;
+    const int levels = g.levels;
     for (;;) {
         if (tid == 0) sh[3] = atomicAdd(&g.queue[0], 1);
         __syncthreads();
@@ -392,9 +349,9 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs g) {
         const int r1 = (K > 1) ? min(n, r0 + D.rbm) : n;
         float *S = g.wsf + D.w_off;
         float *RA = S + (int64_t)n * ld;                       // per level: R then A
-        float *vec = RA + (int64_t)2 * L * n * ld;             // per level: pref, Q, phi, tau, C, B
+        float *vec = RA + (int64_t)2 * levels * n * ld;             // per level: pref, Q, phi, tau, C, B
         int32_t *E = g.wsi + D.i_off;
-        DevState *ds = (DevState *)(E + (int64_t)L * ld);
+        DevState *ds = (DevState *)(E + (int64_t)levels * ld);
         int32_t *sync = (K > 1) ? g.wsi + D.s_off : nullptr;   // [0] barrier counter, [4 + 2m + p] flags
         float *P = (K > 1) ? g.wsf + D.g_off : nullptr;        // column partials [2][K][ld]
         auto R = [&](int l) { return RA + (int64_t)(2 * l) * n * ld; };
@@ -418,7 +375,7 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs g) {
             // 2. Algorithm 1 initial state (alpha = rho = 0, phi = c = 0; tau^1 is never read and
             //    tau^l is written before it is read); padding columns of alpha hold -inf.  Each
             //    member clears its own rows; member 0 the vectors and labels.
-            for (int l = 0; l < L; ++l) {
+            for (int l = 0; l < levels; ++l) {
                 float *Rl = R(l), *Al = A(l);
                 for (int64_t e = (int64_t)r0 * ld + tid; e < (int64_t)r1 * ld; e += NT) {
                     Rl[e] = 0.f;
@@ -442,7 +399,7 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs g) {
             for (int it = 0; it < g.max_iters; ++it) {
                 t += 1;
                 int32_t *chg_flag = (K > 1) ? &sync[4 + 2 * m + (t & 1)] : &ds->changed;
-                for (int l = 0; l < L; ++l) {
+                for (int l = 0; l < levels; ++l) {
                     SweepArgs<float> a;
                     a.S = S;
                     a.lds = ld;
@@ -470,43 +427,28 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs g) {
                     a.lam = g.lam;
                     a.oml = g.oml;
                     a.ds = ds;
-                    V Bv[CH], qv[CH];
-#pragma unroll
-                    for (int c = 0; c < CH; ++c) {
-                        const int j0 = c * NTG * VW + ltid * VW;
-                        Bv[c] = (t > 1 && j0 < n) ? *(const V *)(a.B + j0) : (V)(0.f);
-                        qv[c] = (V)(0.f);
-                    }
-                    if (t == 1)
-                        sweep_rows_grouped<NTG, CH, G, true>(a, t, r0, r1, Bv, qv, gm1, gk1, gm2, gcv, gck, contrib,
-                                                             chg_flag);
+                    // four row groups: rows that one wave holds take a wave each, twice the groups or more
+                    if (G == 4 && n <= 1024)
+                        batch_level<64, 4, NT / 64>(a, t, r0, r1, p, L, chg_flag);
                     else
-                        sweep_rows_grouped<NTG, CH, G, false>(a, t, r0, r1, Bv, qv, gm1, gk1, gm2, gcv, gck, contrib,
-                                                              chg_flag);
-                    __syncthreads();   // c^l, phi^{l-1}, labels of this workgroup's rows are written
+                        batch_level<NTG, CH, G>(a, t, r0, r1, p, L, chg_flag);
                     if (K > 1) {
                         // publish this member's column partials, then meet the gang
-#pragma unroll
-                        for (int c = 0; c < CH; ++c) {
-                            const int j0 = c * NTG * VW + ltid * VW;
-                            if (tid < NTG && j0 < n) *(V *)(P + ((int64_t)par * K + m) * ld + j0) = qv[c];
-                        }
+                        for (int j0 = tid * VW; j0 < n; j0 += NT * VW)
+                            *(V *)(P + ((int64_t)par * K + m) * ld + j0) = L.q[j0 / VW];
                         if (!gang_sync()) goto gave_up;
                     }
-                    // column sums (row group 0: its own in row order, or the members' partials added
-                    // in member order), tau^{l+1}, B^{l-1} and B^l at the top
-#pragma unroll
-                    for (int c = 0; c < CH; ++c) {
-                        const int j0 = c * NTG * VW + ltid * VW;
-                        if (tid >= NTG || j0 >= n) continue;
-                        V tot = qv[c];
+                    // column sums (this workgroup's own, in row order, or the members' partials added in
+                    // member order), tau^{l+1}, B^{l-1} and B^l at the top
+                    for (int j0 = tid * VW; j0 < n; j0 += NT * VW) {
+                        V tot = L.q[j0 / VW];
                         if (K > 1) {
                             tot = *(const V *)(P + ((int64_t)par * K) * ld + j0);
                             for (int k = 1; k < K; ++k) tot += *(const V *)(P + ((int64_t)par * K + k) * ld + j0);
                         }
                         *(V *)(vp(l, 1) + j0) = tot;
-                        if (l + 1 < L) *(V *)(vp(l + 1, 3) + j0) = *(const V *)(vp(l, 4) + j0) + tot;
-                        if (l == L - 1) *(V *)(vp(l, 5) + j0) = tot;
+                        if (l + 1 < levels) *(V *)(vp(l + 1, 3) + j0) = *(const V *)(vp(l, 4) + j0) + tot;
+                        if (l == levels - 1) *(V *)(vp(l, 5) + j0) = tot;
                         if (l > 0)
                             *(V *)(vp(l - 1, 5) + j0) =
                                 (*(const V *)(vp(l - 1, 4) + j0) + *(const V *)(vp(l - 1, 2) + j0)) +
@@ -518,7 +460,7 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs g) {
                 // With two levels no gang barrier separates the column sums of level 1 (which read
                 // c^0 of every row) from the next iteration's level-0 pass (which rewrites c^0 of its
                 // rows); with more levels one does.
-                if (K > 1 && L == 2 && !gang_sync()) goto gave_up;
+                if (K > 1 && levels == 2 && !gang_sync()) goto gave_up;
                 // stop rule: the row passes of iteration t compared the labels of iteration t-1
                 int changed_any;
                 if (K > 1) {
@@ -553,16 +495,18 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs g) {
             // 4. labels of this workgroup's rows: those recorded by the last row pass after an early
             //    stop, otherwise the labels of iteration t from alpha^t finished on the fly
             int32_t *out = g.labels + D.out_off;
-            for (int l = 0; l < L; ++l) {
+            for (int l = 0; l < levels; ++l) {
                 if (stop_iter >= 0) {
                     for (int i = r0 + tid; i < r1; i += NT) out[(int64_t)l * n + i] = E[(int64_t)l * ld + i];
                     continue;
                 }
                 const float *Rl = R(l), *Al = A(l), *Bl = vp(l, 5);
-                for (int i = r0; i < r1; ++i) {
+                // a wave per row
+                for (int i = r0 + wid; i < r1; i += NW) {
                     float cv = neg_inf<float>();
                     int ck = INT_MAX;
-                    for (int j = tid; j < n; j += NT) {
+#pragma unroll 4
+                    for (int j = lane; j < n; j += 64) {
                         const float rj = Rl[(int64_t)i * ld + j];
                         float al = Al[(int64_t)i * ld + j];
                         if (t >= 1) {
@@ -581,25 +525,15 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs g) {
                         const int ock = __shfl_xor(ck, off, 64);
                         argmax_merge(cv, ck, ocv, ock);
                     }
-                    if (lane == 0) {
-                        sh_cv[0][wid] = cv;
-                        sh_ck[0][wid] = ck;
-                    }
-                    __syncthreads();
-                    if (tid == 0) {
-                        cv = sh_cv[0][0];
-                        ck = sh_ck[0][0];
-                        for (int w = 1; w < NW; ++w) argmax_merge(cv, ck, sh_cv[0][w], sh_ck[0][w]);
-                        out[(int64_t)l * n + i] = ck;
-                    }
-                    __syncthreads();
+                    if (lane == 0) out[(int64_t)l * n + i] = ck;
                 }
             }
+            __syncthreads();
             if (!gang_sync()) goto gave_up;
             // 5. net similarity per level and total, FP64, fixed-order reduction (member 0)
             if (m == 0) {
                 double total = 0.0;
-                for (int l = 0; l < L; ++l) {
+                for (int l = 0; l < levels; ++l) {
                     double acc = 0.0;
                     for (int i = tid; i < n; i += NT) {
                         const int e = out[(int64_t)l * n + i];
@@ -615,13 +549,13 @@ __global__ __launch_bounds__(NT) void batch_kernel(BatchArgs g) {
                     if (tid == 0) {
                         double s2 = 0.0;
                         for (int w = 0; w < NW; ++w) s2 += shd[w];
-                        g.ns[(int64_t)b * (L + 1) + l] = s2;
+                        g.ns[(int64_t)b * (levels + 1) + l] = s2;
                         total += s2;
                     }
                     __syncthreads();
                 }
                 if (tid == 0) {
-                    g.ns[(int64_t)b * (L + 1) + L] = total;
+                    g.ns[(int64_t)b * (levels + 1) + levels] = total;
                     g.iters[b] = stop_iter >= 0 ? stop_iter : t;
                 }
             }
