@@ -1698,7 +1698,7 @@ hap_status hap_mlp_train(float *params, float *opt_state, int32_t n_in, int32_t 
     for (int64_t s = 0; s < steps; ++s) {
         const hipError_t e = hap::mlp_train_step(lo, n_in, hidden, n_out, precision == HAP_BF16, params, opt_state,
                                                  opt_state + lo.count, step0 + s + 1, X, ldx, T, ldt, (int)rows,
-                                                 idx + s * batch, (int)batch, lr, loss_hist ? loss_hist + s : nullptr, ws,
+                                                 idx + s * batch, (int)batch, lr, loss_hist ? loss_hist + s : nullptr, s == 0, ws,
                                                  workspace_bytes, st);
         if (e != hipSuccess) return fail_hip(e, "hap_mlp_train");
     }

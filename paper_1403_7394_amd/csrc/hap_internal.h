@@ -271,10 +271,10 @@ hipError_t mlp_loss_grad(const MlpLayout &lo, int n_in, int hidden, int n_out, b
 hipError_t mlp_adam(float *P, const float *G, float *M, float *V, int64_t count, int64_t step, double lr, double b1,
                     double b2, double eps, hipStream_t st);
 // One minibatch step: the rows idx[0..batch) of X and T (an index outside [0, rows) reads as NaN),
-// loss and gradient, Adam step `step` (beta1 0.9, beta2 0.999, eps 1e-8); *loss (or nothing, nullptr) is written.
+// loss and gradient, Adam step `step`, the `first` of a call or a later one on the same workspace (beta1 0.9, beta2 0.999, eps 1e-8); *loss (or nothing, nullptr) is written.
 hipError_t mlp_train_step(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, float *P, float *M, float *V,
                           int64_t step, const float *X, int64_t ldx, const float *T, int64_t ldt, int rows,
-                          const int32_t *idx, int batch, double lr, double *loss, char *ws, size_t ws_bytes,
+                          const int32_t *idx, int batch, double lr, double *loss, bool first, char *ws, size_t ws_bytes,
                           hipStream_t st);
 
 // Warm start (warm.hip).  Features of every row of S (n x HAP_WARM_FEATURES floats) with

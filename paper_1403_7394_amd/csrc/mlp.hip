@@ -209,7 +209,8 @@ __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ P, const 
 // 32 -> 128 -> 128 -> 3 at 4096 rows (1.96 ms) in its weight gradients: a 128 x 128 product over
 // 4096 rows is four 64 x 64 tiles, four workgroups that each wait for 128 loads in turn.  The
 // chain itself (128 MFMAs of 8 passes) takes 2 us; both kernels here are bound by latency.  Measured
-// in BF16: that step 1.96 ms -> 39 us (tiles 26 us, gradients and Adam 14 us), the prediction of 65536
+// in BF16: that step 1.96 ms -> 28 us (tiles 17 us, 26 while every workgroup gathered and rounded the FP32
+// weights; gradients and Adam 11 us, 14 with fewer loads in flight), the prediction of 65536
 // rows 99 -> 18 us (layer by layer H1 and H2 travel through memory, 134 MB).
 // ---------------------------------------------------------------------------
 constexpr int kTile = 32;   // rows of a tile: one k step of the BF16 MFMA
@@ -281,7 +282,16 @@ struct FuseLayout {
     int tiles, bh;         // tiles of rows; blocks of hidden units
     int64_t rows;          // tiles * kTile
     size_t X, H1, H2, dY, d1, d2, f1, f2, fy, loss, bytes;
+    // BF16 only: W1, W2 and W2^T rounded and in fragment order for the tile kernel, which the gradient
+    // kernel keeps up to date over the steps of one training call
+    size_t p1, p2, p2t, bytes_packed;
 };
+// hidden units as the tile kernel is built for them
+inline int padded_hidden(int hidden) { return hidden <= 64 ? 64 : hidden <= 128 ? 128 : 256; }
+// element (k, col) of an operand of nk k steps of 32, in fragment order
+__host__ __device__ inline int frag_at(int col, int k, int nk) {
+    return ((col >> 4) * nk + (k >> 5)) * 512 + (((k & 31) >> 3) * 16 + (col & 15)) * 8 + (k & 7);
+}
 FuseLayout fuse_layout(int hidden, int n_out, int64_t rows, bool bf16) {
     FuseLayout f{};
     f.tiles = (int)((rows + kTile - 1) / kTile);
@@ -305,6 +315,11 @@ FuseLayout fuse_layout(int hidden, int n_out, int64_t rows, bool bf16) {
     f.fy = take((size_t)f.rows * n_out * 4);
     f.loss = take((size_t)f.tiles * 8);
     f.bytes = off;
+    const int hp = padded_hidden(hidden);
+    f.p1 = take((size_t)hp * kFuseIn * 2);
+    f.p2 = take((size_t)hp * hp * 2);
+    f.p2t = take((size_t)hp * hp * 2);
+    f.bytes_packed = bf16 ? off : f.bytes;
     return f;
 }
 
@@ -326,7 +341,7 @@ struct FuseArgs {
     char *ws;
 };
 
-template <bool BF16, int HP, bool TRAIN>
+template <bool BF16, int HP, bool TRAIN, bool PACKED>
 __global__ __launch_bounds__(2 * HP) void mlp_tile_kernel(FuseArgs g) {
     using M = Mx<BF16>;
     using E = typename M::E;
@@ -360,9 +375,26 @@ __global__ __launch_bounds__(2 * HP) void mlp_tile_kernel(FuseArgs g) {
     // Weight fragments: in registers over the tiles (they are the same for every tile), except
     // where they do not fit (training at 256 units), which reads them where they are used.
     constexpr bool KEEP = HP <= 128 || !TRAIN;
-    auto read_w2 = [&](int k, int c) { return M::global(W2 + colc[c], H, k * KS, kg, H, col[c] < H); };
+    auto packed = [&](size_t region, int k, int c, int nk) {
+        return *(const F *)((const E *)(g.ws + region) + (((wid * 2 + c) * nk + k) * 64 + lane) * 8);
+    };
+    auto read_w1 = [&](int k, int c) {
+        if constexpr (PACKED)
+            return packed(g.fl.p1, k, c, NKI);
+        else
+            return M::global(W1 + colc[c], H, k * KS, kg, n_in, col[c] < H);
+    };
+    auto read_w2 = [&](int k, int c) {
+        if constexpr (PACKED)
+            return packed(g.fl.p2, k, c, NKH);
+        else
+            return M::global(W2 + colc[c], H, k * KS, kg, H, col[c] < H);
+    };
     auto read_w2t = [&](int k, int c) {
-        return M::global(W2 + colc[c] * H, 1, k * KS, kg, H, col[c] < H);
+        if constexpr (PACKED)
+            return packed(g.fl.p2t, k, c, NKH);
+        else
+            return M::global(W2 + colc[c] * H, 1, k * KS, kg, H, col[c] < H);
     };
     auto read_w3 = [&](int k) { return M::global(W3 + outc, n_out, k * KS, kg, H, r16 < n_out); };
     F w1[NKI][2], w2[KEEP ? NKH : 1][2], w3[KEEP ? NKH : 1];
@@ -370,7 +402,7 @@ __global__ __launch_bounds__(2 * HP) void mlp_tile_kernel(FuseArgs g) {
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
-        for (int k = 0; k < NKI; ++k) w1[k][c] = M::global(W1 + colc[c], H, k * KS, kg, n_in, col[c] < H);
+        for (int k = 0; k < NKI; ++k) w1[k][c] = read_w1(k, c);
     if constexpr (KEEP) {
 #pragma unroll
         for (int k = 0; k < NKH; ++k) {
@@ -455,7 +487,7 @@ __global__ __launch_bounds__(2 * HP) void mlp_tile_kernel(FuseArgs g) {
 #pragma unroll
                 for (int k = 0; k < NKH; ++k) step(k, kept[k]);
             } else {
-#pragma unroll(BF16 ? 1 : 8)
+#pragma unroll(BF16 && !PACKED ? 1 : 8)
                 for (int k = 0; k < NKH; ++k) {
                     const F b[2] = {read(k, 0), read(k, 1)};
                     step(k, b);
@@ -555,6 +587,20 @@ __global__ __launch_bounds__(2 * HP) void mlp_tile_kernel(FuseArgs g) {
     }
 }
 
+// W1, W2 and W2^T rounded to BF16 in fragment order, zero past their ends.
+__global__ __launch_bounds__(256) void mlp_pack_kernel(const float *P, MlpLayout lo, FuseLayout fl, int n_in, int H,
+                                                       int hp, char *ws) {
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e >= hp * hp) return;
+    const int k = e / hp, c = e % hp, nk = hp / 32;
+    const float *W1 = P + lo.oW1, *W2 = P + lo.oW2;
+    const bool in = k < H && c < H;
+    const __bf16 v = rne_bf16(in ? W2[(int64_t)k * H + c] : 0.f);
+    ((__bf16 *)(ws + fl.p2))[frag_at(c, k, nk)] = v;
+    ((__bf16 *)(ws + fl.p2t))[frag_at(k, c, nk)] = v;
+    if (k < kFuseIn) ((__bf16 *)(ws + fl.p1))[frag_at(c, k, 1)] = rne_bf16(k < n_in && c < H ? W1[(int64_t)k * H + c] : 0.f);
+}
+
 struct GradArgs {
     MlpLayout lo;
     FuseLayout fl;
@@ -564,6 +610,8 @@ struct GradArgs {
     float *G;                 // gradient (no ADAM)
     float *P, *Mv, *Vv;       // ADAM
     AdamArgs ad;
+    char *pack;               // the workspace where the packed weights are to follow, or nullptr
+    int hp;
 };
 
 // Parameter gradients from a batch's operands.  Workgroups, in order: one per 16 x 16 tile of
@@ -601,7 +649,7 @@ __global__ __launch_bounds__(256) void mlp_grad_kernel(GradArgs g) {
         const F *A = (const F *)((const E *)(g.ws + ra) + (int64_t)ba * g.fl.tiles * kFrag) + lane;
         const F *B = (const F *)((const E *)(g.ws + rb) + (int64_t)bb * g.fl.tiles * kFrag) + lane;
         f32x4 acc = (f32x4){0.f, 0.f, 0.f, 0.f};
-        constexpr int UN = BF16 ? 16 : 2;    // tiles of rows in flight
+        constexpr int UN = BF16 ? 24 : 4;    // tiles of rows in flight
         int t = 0;
         for (; t + UN <= g.fl.tiles; t += UN) {
             F fa[UN * PER], fb[UN * PER];
@@ -610,6 +658,7 @@ __global__ __launch_bounds__(256) void mlp_grad_kernel(GradArgs g) {
                 fa[k] = A[((int64_t)t * PER + k) * 64];
                 fb[k] = B[((int64_t)t * PER + k) * 64];
             }
+            __builtin_amdgcn_sched_barrier(0);   // every load before the first product
 #pragma unroll
             for (int k = 0; k < UN * PER; ++k) acc = M::mma(fa[k], fb[k], acc);
         }
@@ -621,7 +670,21 @@ __global__ __launch_bounds__(256) void mlp_grad_kernel(GradArgs g) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int m = 16 * ba + 4 * (lane >> 4) + r;
-            if (m < M_ && n < N_) emit(out + (int64_t)m * N_ + n, acc[r]);
+            if (m < M_ && n < N_) {
+                const int64_t i = out + (int64_t)m * N_ + n;
+                emit(i, acc[r]);
+                if constexpr (BF16 && ADAM) {
+                    if (g.pack && rb != g.fl.dY) {
+                        const __bf16 w = rne_bf16(g.P[i]);
+                        if (rb == g.fl.d2) {
+                            ((__bf16 *)(g.pack + g.fl.p2))[frag_at(n, m, g.hp / 32)] = w;
+                            ((__bf16 *)(g.pack + g.fl.p2t))[frag_at(m, n, g.hp / 32)] = w;
+                        } else {
+                            ((__bf16 *)(g.pack + g.fl.p1))[frag_at(n, m, 1)] = w;
+                        }
+                    }
+                }
+            }
         }
         return;
     }
@@ -713,17 +776,25 @@ bool fuse_ok(int n_in, int hidden, int n_out) {
 // At most 1024 workgroups (about four per CU of the 256): past that a workgroup takes several
 // tiles and reads the weights once for all of them.
 template <bool BF16, int HP, bool TRAIN>
-hipError_t launch_tile(const FuseArgs &g, hipStream_t st) {
+hipError_t launch_tile(const FuseArgs &g, bool packed, hipStream_t st) {
     const int grid = g.tiles < 1024 ? g.tiles : 1024;
-    hipLaunchKernelGGL((mlp_tile_kernel<BF16, HP, TRAIN>), dim3(grid), dim3(2 * HP), 0, st, g);
+    if constexpr (BF16 && TRAIN) {
+        if (packed) {
+            hipLaunchKernelGGL((mlp_tile_kernel<BF16, HP, TRAIN, true>), dim3(grid), dim3(2 * HP), 0, st, g);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((mlp_tile_kernel<BF16, HP, TRAIN, false>), dim3(grid), dim3(2 * HP), 0, st, g);
     return hipGetLastError();
 }
 
 template <bool TRAIN>
-hipError_t run_tiles(bool bf16, const FuseArgs &g, hipStream_t st) {
-    if (g.H <= 64) return bf16 ? launch_tile<true, 64, TRAIN>(g, st) : launch_tile<false, 64, TRAIN>(g, st);
-    if (g.H <= 128) return bf16 ? launch_tile<true, 128, TRAIN>(g, st) : launch_tile<false, 128, TRAIN>(g, st);
-    return bf16 ? launch_tile<true, 256, TRAIN>(g, st) : launch_tile<false, 256, TRAIN>(g, st);
+hipError_t run_tiles(bool bf16, const FuseArgs &g, bool packed, hipStream_t st) {
+    const int hp = padded_hidden(g.H);
+    if (hp == 64) return bf16 ? launch_tile<true, 64, TRAIN>(g, packed, st) : launch_tile<false, 64, TRAIN>(g, false, st);
+    if (hp == 128)
+        return bf16 ? launch_tile<true, 128, TRAIN>(g, packed, st) : launch_tile<false, 128, TRAIN>(g, false, st);
+    return bf16 ? launch_tile<true, 256, TRAIN>(g, packed, st) : launch_tile<false, 256, TRAIN>(g, false, st);
 }
 
 FuseArgs fuse_args(const MlpLayout &lo, int n_in, int hidden, int n_out, const float *P, const float *X, int64_t ldx,
@@ -743,10 +814,13 @@ FuseArgs fuse_args(const MlpLayout &lo, int n_in, int hidden, int n_out, const f
 }
 
 // Loss and gradient (G), or loss and Adam step (P, Mv, Vv) of `rows` rows, idx[r] of X and T if idx.
+// packed: the tile kernel reads the packed weights, which this call makes anew (fresh) or finds as the
+// last call's Adam step left them.
 template <bool ADAM>
 hipError_t run_train(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, const float *P, const float *X,
                      int64_t ldx, const float *T, int64_t ldt, const int32_t *idx, int rows, int x_rows, double *loss,
-                     float *G, float *Pw, float *Mv, float *Vv, const AdamArgs &ad, char *ws, hipStream_t st) {
+                     float *G, float *Pw, float *Mv, float *Vv, const AdamArgs &ad, bool packed, bool fresh, char *ws,
+                     hipStream_t st) {
     FuseArgs g = fuse_args(lo, n_in, hidden, n_out, P, X, ldx, rows);
     g.idx = idx;
     g.x_rows = x_rows;
@@ -755,7 +829,12 @@ hipError_t run_train(const MlpLayout &lo, int n_in, int hidden, int n_out, bool 
     g.scale = (float)(2.0 / ((double)rows * n_out));
     g.fl = fuse_layout(hidden, n_out, rows, bf16);
     g.ws = ws;
-    MLP_TRY(run_tiles<true>(bf16, g, st));
+    const int hp = padded_hidden(hidden);
+    if (packed && fresh) {
+        hipLaunchKernelGGL(mlp_pack_kernel, dim3((hp * hp + 255) / 256), dim3(256), 0, st, P, lo, g.fl, n_in, hidden, hp, ws);
+        MLP_TRY(hipGetLastError());
+    }
+    MLP_TRY(run_tiles<true>(bf16, g, packed, st));
     GradArgs a{};
     a.lo = lo;
     a.fl = g.fl;
@@ -770,6 +849,8 @@ hipError_t run_train(const MlpLayout &lo, int n_in, int hidden, int n_out, bool 
     a.Mv = Mv;
     a.Vv = Vv;
     a.ad = ad;
+    a.pack = packed ? ws : nullptr;
+    a.hp = hp;
     const int bh = g.fl.bh;
     const int grid = bh * bh + (n_in + 15) / 16 * bh + bh + 2 * hidden + n_out + 1;
     if (bf16)
@@ -814,7 +895,7 @@ MlpLayout mlp_layout(int n_in, int hidden, int n_out, int64_t rows) {
 size_t mlp_workspace_bytes(int n_in, int hidden, int n_out, int64_t rows) {
     size_t b = mlp_layout(n_in, hidden, n_out, rows).bytes;
     if (fuse_ok(n_in, hidden, n_out))
-        for (const bool bf16 : {false, true}) b = std::max(b, fuse_layout(hidden, n_out, rows, bf16).bytes);
+        for (const bool bf16 : {false, true}) b = std::max(b, fuse_layout(hidden, n_out, rows, bf16).bytes_packed);
     return b;
 }
 
@@ -841,7 +922,7 @@ hipError_t mlp_forward(const MlpLayout &lo, int n_in, int hidden, int n_out, boo
     FuseArgs g = fuse_args(lo, n_in, hidden, n_out, P, X, ldx, rows);
     g.Y = Y;
     g.ldy = ldy;
-    return run_tiles<false>(bf16, g, st);
+    return run_tiles<false>(bf16, g, false, st);
 }
 
 namespace {
@@ -859,7 +940,7 @@ hipError_t mlp_loss_grad(const MlpLayout &lo, int n_in, int hidden, int n_out, b
     const int H = hidden;
     if (fuse_ok(n_in, hidden, n_out) && ws_bytes >= fuse_layout(hidden, n_out, rows, bf16).bytes)
         return run_train<false>(lo, n_in, hidden, n_out, bf16, P, X, ldx, T, ldt, nullptr, rows, rows, loss, G, nullptr,
-                                nullptr, nullptr, AdamArgs{}, ws, st);
+                                nullptr, nullptr, AdamArgs{}, false, false, ws, st);
     float *H1 = (float *)(ws + lo.H1), *H2 = (float *)(ws + lo.H2), *Y = (float *)(ws + lo.Y);
     float *dY = (float *)(ws + lo.dY), *dH2 = (float *)(ws + lo.dH2), *dH1 = (float *)(ws + lo.dH1);
     MLP_TRY(layered_forward(lo, n_in, hidden, n_out, bf16, P, X, ldx, rows, Y, n_out, ws, st));
@@ -905,12 +986,13 @@ hipError_t mlp_gather(const float *X, int64_t ldx, int w, const int32_t *idx, in
 
 hipError_t mlp_train_step(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, float *P, float *M, float *V,
                           int64_t step, const float *X, int64_t ldx, const float *T, int64_t ldt, int rows,
-                          const int32_t *idx, int batch, double lr, double *loss, char *ws, size_t ws_bytes,
+                          const int32_t *idx, int batch, double lr, double *loss, bool first, char *ws, size_t ws_bytes,
                           hipStream_t st) {
     float *G = (float *)(ws + lo.G);
-    if (fuse_ok(n_in, hidden, n_out) && ws_bytes >= fuse_layout(hidden, n_out, batch, bf16).bytes)
+    const FuseLayout fl = fuse_layout(hidden, n_out, batch, bf16);
+    if (fuse_ok(n_in, hidden, n_out) && ws_bytes >= fl.bytes)
         return run_train<true>(lo, n_in, hidden, n_out, bf16, P, X, ldx, T, ldt, idx, batch, rows, loss, nullptr, P, M, V,
-                               adam_args(step, lr, 0.9, 0.999, 1e-8), ws, st);
+                               adam_args(step, lr, 0.9, 0.999, 1e-8), bf16 && ws_bytes >= fl.bytes_packed, first, ws, st);
     float *Xb = (float *)(ws + lo.Xb), *Tb = (float *)(ws + lo.Tb);
     MLP_TRY(mlp_gather(X, ldx, n_in, idx, batch, rows, Xb, st));
     MLP_TRY(mlp_gather(T, ldt, n_out, idx, batch, rows, Tb, st));
