@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ P, const 
 // chain itself (128 MFMAs of 8 passes) takes 2 us; both kernels here are bound by latency.  Measured
 // in BF16: that step 1.96 ms -> 28 us (tiles 17 us, 26 while every workgroup gathered and rounded the FP32
 // weights; gradients and Adam 11 us, 14 with fewer loads in flight), the prediction of 65536
-// rows 99 -> 18 us (layer by layer H1 and H2 travel through memory, 134 MB).
+// rows 99 -> 13 us (layer by layer H1 and H2 travel through memory, 134 MB).
 // ---------------------------------------------------------------------------
 constexpr int kTile = 32;   // rows of a tile: one k step of the BF16 MFMA
 
@@ -773,11 +773,20 @@ bool fuse_ok(int n_in, int hidden, int n_out) {
     return n_in <= kFuseIn && hidden <= kFuseHidden && n_out <= kFuseOut;
 }
 
-// At most 1024 workgroups (about four per CU of the 256): past that a workgroup takes several
-// tiles and reads the weights once for all of them.
+// As many workgroups as the 256 CUs hold at once (by the registers of each instance): past that a
+// workgroup takes several tiles and reads the weights once for all of them.  Forward passes of 65536
+// rows in BF16 with 128 units: 13.7 us with these 768, 16.3 with 512, 19.6 with 1024 (a second, nearly
+// empty wave); 256 units: 28.3 with 256, 51.2 with 1024.
+template <bool BF16, int HP, bool TRAIN>
+constexpr int tile_workgroups() {
+    const int waves = TRAIN ? ((BF16 || HP != 128) ? 2 : 1) : HP == 256 ? 2 : BF16 ? 3 : HP == 64 ? 4 : 2;   // per SIMD
+    return 256 * (waves * 4 * 32 / HP);
+}
+
 template <bool BF16, int HP, bool TRAIN>
 hipError_t launch_tile(const FuseArgs &g, bool packed, hipStream_t st) {
-    const int grid = g.tiles < 1024 ? g.tiles : 1024;
+    constexpr int most = tile_workgroups<BF16, HP, TRAIN>();
+    const int grid = g.tiles < most ? g.tiles : most;
     if constexpr (BF16 && TRAIN) {
         if (packed) {
             hipLaunchKernelGGL((mlp_tile_kernel<BF16, HP, TRAIN, true>), dim3(grid), dim3(2 * HP), 0, st, g);
