@@ -41,6 +41,15 @@ struct FlowLds {
     T p[kWin], tau[kWin], d[kWin], xi[kWin][D > 0 ? D : 1];  // per-row scalars
     int e[kWin], has[kWin];
 };
+// One row per group: nothing staged, and a slab of contributions per group instead of turns.
+template <typename T, int NTG, int NCH, int RG>
+struct FlowOneLds {
+    static constexpr int NWG = NTG / 64;
+    typename Vec<T>::type q[RG][NCH][NTG];
+    T m1[RG][NWG], m2[RG][NWG], cv[RG][NWG];
+    int ck[RG][NWG];
+    int arrived[RG];
+};
 
 // This wave's LDS accesses are done and stay on their side of this point (global accesses in flight are
 // not waited for).
@@ -203,10 +212,9 @@ __device__ __forceinline__ void flow_phase2(FlowRow<T, NTG, NCH> &x, int i, int 
     }
 }
 
-// ONE: no group has more than one row, which the caller has loaded into x.
-template <typename T, int NTG, int NCH, int RG, bool FIRST, bool TAIL, int D, bool ONE>
+template <typename T, int NTG, int NCH, int RG, bool FIRST, bool TAIL, int D>
 __device__ __forceinline__ void flow_rows(const SweepArgs<T> &a, const int t, const int row0, const int row1,
-                                          const typename Vec<T>::type (&Bv)[NCH], FlowRow<T, NTG, NCH> &first,
+                                          const typename Vec<T>::type (&Bv)[NCH],
                                           FlowLds<T, NTG, NCH, RG, D> &L) {
 #pragma clang fp contract(off)
     using V = typename Vec<T>::type;
@@ -228,9 +236,7 @@ __device__ __forceinline__ void flow_rows(const SweepArgs<T> &a, const int t, co
         const __amdgpu_buffer_rsrc_t rR = row_rsrc(a.R + (int64_t)i * ldw, row_bytes);
         const __amdgpu_buffer_rsrc_t rA = row_rsrc(a.A + (int64_t)i * ldw, row_bytes);
         FlowRow<T, NTG, NCH> x;
-        if constexpr (ONE) {
-            x = first;
-        } else {
+        {
             const __amdgpu_buffer_rsrc_t rS = row_rsrc(a.S + (int64_t)i * a.lds, row_bytes);
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
@@ -316,42 +322,22 @@ __device__ __forceinline__ void flow_rows(const SweepArgs<T> &a, const int t, co
             lds_settle();
             if (lane == 0) __hip_atomic_store(&L.turn[wid], r + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         }
-        if constexpr (ONE) break;
     }
     if (chg) atomicOr(&a.ds->changed, 1);
 }
 
-template <typename T, int NTG, int NCH, int RG, bool TAIL, int D, bool ONE>
+template <typename T, int NTG, int NCH, int RG, bool TAIL, int D>
 __global__ __launch_bounds__(NTG *RG) void sweep_flow_kernel(SweepArgs<T> a) {
 #pragma clang fp contract(off)
     using V = typename Vec<T>::type;
     constexpr int VW = Vec<T>::N;
     constexpr int NT = NTG * RG;
-    constexpr int CB = NTG * VW * (int)sizeof(T);
     __shared__ __attribute__((aligned(16))) FlowLds<T, NTG, NCH, RG, D> L;
     const int tid = threadIdx.x, ltid = tid % NTG;
     const int n = a.n;
     const int row0 = blockIdx.x * a.rb;
     const int row1 = slots_end(a.rows, a.rb, row0, a.row_stride);
     const DevState *ds = a.ds;
-    FlowRow<T, NTG, NCH> x;
-    if constexpr (ONE) {
-        // the rows do not depend on the iteration state: their loads go first
-        const int64_t row_bytes = (int64_t)((n + VW - 1) / VW * VW) * (int)sizeof(T);
-        const int grp = RG > 1 ? __builtin_amdgcn_readfirstlane(tid / NTG) : 0;
-        if (row0 + grp < row1) {
-            const int i = slot_row(row0 + grp, row0, a.rb, a.row_stride);
-            const __amdgpu_buffer_rsrc_t rR = row_rsrc(a.R + (int64_t)i * a.ldw, row_bytes);
-            const __amdgpu_buffer_rsrc_t rA = row_rsrc(a.A + (int64_t)i * a.ldw, row_bytes);
-            const __amdgpu_buffer_rsrc_t rS = row_rsrc(a.S + (int64_t)i * a.lds, row_bytes);
-#pragma unroll
-            for (int c = 0; c < NCH; ++c) {
-                if constexpr (D <= 0) x.s[c] = buf_load<V, flow_policy<NTG>()>(rS, ltid * 16, c * CB);
-                x.r[c] = buf_load<V, flow_policy<NTG>()>(rR, ltid * 16, c * CB);
-                x.a[c] = buf_load<V, flow_policy<NTG>()>(rA, ltid * 16, c * CB);
-            }
-        }
-    }
     V Bv[NCH];
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
@@ -383,9 +369,9 @@ __global__ __launch_bounds__(NTG *RG) void sweep_flow_kernel(SweepArgs<T> a) {
     }
     __syncthreads();
     if (t == 1)
-        flow_rows<T, NTG, NCH, RG, true, TAIL, D, ONE>(a, t, row0, row1, Bv, x, L);
+        flow_rows<T, NTG, NCH, RG, true, TAIL, D>(a, t, row0, row1, Bv, L);
     else
-        flow_rows<T, NTG, NCH, RG, false, TAIL, D, ONE>(a, t, row0, row1, Bv, x, L);
+        flow_rows<T, NTG, NCH, RG, false, TAIL, D>(a, t, row0, row1, Bv, L);
     __syncthreads();
     T *qrow = a.Qpart + (int64_t)blockIdx.x * a.ldw;
     for (int e = tid; e < NCH * NTG; e += NT) {
@@ -395,25 +381,166 @@ __global__ __launch_bounds__(NTG *RG) void sweep_flow_kernel(SweepArgs<T> a) {
     }
 }
 
+// At most one row per group (the default up to 2048 points): a chain of latencies, so every load goes out
+// before the first is waited for, the row's scalars come straight from memory, and the contributions are
+// added in row order from a slab per group after one barrier.  788 points: 7.9 us a launch with staged
+// scalars and turns, 6.0 us here.  Reads S: in points mode the columns' coordinates are better staged in
+// LDS (2000 points, with column sums, 19.1 us a level against 29.7 with every lane gathering its own).
+template <typename T, int NTG, int NCH, int RG, bool FIRST, bool TAIL, int D>
+__device__ __forceinline__ void flow_one(const SweepArgs<T> &a, const int t, const int i, FlowRow<T, NTG, NCH> &x,
+                                         const typename Vec<T>::type (&Bv)[NCH], const T p_i, const T d_i,
+                                         const int e_old, const bool has_tau, const T tau_i,
+                                         FlowOneLds<T, NTG, NCH, RG> &L) {
+#pragma clang fp contract(off)
+    using V = typename Vec<T>::type;
+    constexpr int VW = Vec<T>::N, NWG = NTG / 64;
+    const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x / NTG);
+    const int ltid = threadIdx.x % NTG, lane = ltid & 63, wid = __builtin_amdgcn_readfirstlane(ltid >> 6);
+    const int n = a.n;
+    const int base = ltid * VW, voff = ltid * 16;
+    const int64_t row_bytes = (int64_t)((n + VW - 1) / VW * VW) * (int)sizeof(T);
+    const __amdgpu_buffer_rsrc_t rR = row_rsrc(a.R + (int64_t)i * a.ldw, row_bytes);
+    const __amdgpu_buffer_rsrc_t rA = row_rsrc(a.A + (int64_t)i * a.ldw, row_bytes);
+    T m1, m2, cv;
+    int ck;
+    flow_phase1<T, NTG, NCH, FIRST, TAIL, (D < 0)>(
+        x, i, n, wid, base, a.lam, a.oml, p_i, d_i, rA, voff, m1, m2, cv, ck,
+        [&](int, V &) {}, [&](int c) { return Bv[c]; });
+    ck = (ck == INT_MAX) ? INT_MAX : ck + base;
+    flow_reduce<T, !FIRST>(m1, m2, cv, ck);
+    if constexpr (NWG > 1) {
+        if (lane == 63) {
+            L.m1[grp][wid] = m1;
+            L.m2[grp][wid] = m2;
+            L.cv[grp][wid] = cv;
+            L.ck[grp][wid] = ck;
+        }
+        lds_settle();
+        if (lane == 0) __hip_atomic_fetch_add(&L.arrived[grp], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        lds_wait(&L.arrived[grp], NWG);
+        m1 = L.m1[grp][0];
+        m2 = L.m2[grp][0];
+#pragma unroll
+        for (int w = 1; w < NWG; ++w) pair_merge(m1, m2, L.m1[grp][w], L.m2[grp][w]);
+    } else {
+        m1 = lane63(m1);
+        m2 = lane63(m2);
+    }
+    flow_phase2<T, NTG, NCH, TAIL>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fmin(tau_i, -m1) : -m1,
+                                   has_tau ? fmin(tau_i, -m2) : -m2, rR, voff);
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) L.q[grp][c][ltid] = x.s[c];
+    if (ltid == 63) {
+        if constexpr (!FIRST) {
+            if constexpr (NWG > 1) {
+                cv = L.cv[grp][0];
+                ck = L.ck[grp][0];
+                for (int w = 1; w < NWG; ++w) argmax_merge(cv, ck, L.cv[grp][w], L.ck[grp][w]);
+            }
+            a.C[i] = cv;
+            a.E[i] = ck;
+            if (t >= 3 && e_old != ck) atomicOr(&a.ds->changed, 1);
+        }
+        if (a.phi_down && (!FIRST || a.mrhap)) a.phi_down[i] = m1;
+        if (a.tau_store) a.tau_store[i] = has_tau ? tau_i : pos_inf<T>();
+    }
+}
+
+template <typename T, int NTG, int NCH, int RG, bool TAIL, int D>
+__global__ __launch_bounds__(NTG *RG) void sweep_flow_one_kernel(SweepArgs<T> a) {
+#pragma clang fp contract(off)
+    using V = typename Vec<T>::type;
+    constexpr int VW = Vec<T>::N, NT = NTG * RG;
+    constexpr int CB = NTG * VW * (int)sizeof(T);
+    static_assert(D <= 0, "reads S");
+    __shared__ __attribute__((aligned(16))) FlowOneLds<T, NTG, NCH, RG> L;
+    const int tid = threadIdx.x, ltid = tid % NTG;
+    const int grp = __builtin_amdgcn_readfirstlane(tid / NTG);
+    const int n = a.n;
+    const int row0 = blockIdx.x * a.rb;
+    const int row1 = slots_end(a.rows, a.rb, row0, a.row_stride);
+    const DevState *ds = a.ds;
+    const int done = ds->done, t = ds->t + 1;
+    const bool mine = row0 + grp < row1;   // this group has a row
+    const int i = slot_row(mine ? row0 + grp : row0, row0, a.rb, a.row_stride);
+    const int64_t row_bytes = (int64_t)((n + VW - 1) / VW * VW) * (int)sizeof(T);
+    FlowRow<T, NTG, NCH> x;
+    V Bv[NCH];
+    T p_i = T(0), d_i = T(0), tau_i = T(0);
+    int e_old = 0;
+    const bool mr = a.tau_c != nullptr;
+    if (mine) {
+        const __amdgpu_buffer_rsrc_t rR = row_rsrc(a.R + (int64_t)i * a.ldw, row_bytes);
+        const __amdgpu_buffer_rsrc_t rA = row_rsrc(a.A + (int64_t)i * a.ldw, row_bytes);
+        const __amdgpu_buffer_rsrc_t rS = row_rsrc(a.S + (int64_t)i * a.lds, row_bytes);
+        const __amdgpu_buffer_rsrc_t rB = row_rsrc(a.B, row_bytes);
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            x.s[c] = buf_load<V, flow_policy<NTG>()>(rS, ltid * 16, c * CB);
+            x.r[c] = buf_load<V, flow_policy<NTG>()>(rR, ltid * 16, c * CB);
+            x.a[c] = buf_load<V, flow_policy<NTG>()>(rA, ltid * 16, c * CB);
+            Bv[c] = buf_load<V, 0>(rB, ltid * 16, c * CB);
+        }
+        p_i = a.pref[i];
+        if constexpr (D < 0) d_i = a.delta[i];
+        e_old = a.E[i];
+        // the upward message (row_tau), loaded whether or not this iteration clips with it
+        if (mr)
+            tau_i = a.tau_c[i] + a.tau_q[i];
+        else if (a.tau != nullptr)
+            tau_i = a.tau[i];
+    }
+    if (done) return;
+    if constexpr (NTG > 64) {
+        if (tid < RG) L.arrived[tid] = 0;
+        lds_settle();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
+    const bool has_tau = mr ? t >= 2 : a.tau != nullptr;
+    if (mine) {
+        if (t == 1)
+            flow_one<T, NTG, NCH, RG, true, TAIL, D>(a, t, i, x, Bv, p_i, d_i, e_old, has_tau, tau_i, L);
+        else
+            flow_one<T, NTG, NCH, RG, false, TAIL, D>(a, t, i, x, Bv, p_i, d_i, e_old, has_tau, tau_i, L);
+    }
+    lds_settle();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    T *qrow = a.Qpart + (int64_t)blockIdx.x * a.ldw;
+    const int groups = row1 - row0;
+    for (int e = tid; e < NCH * NTG; e += NT) {
+        const int c = e / NTG, lt = e % NTG;
+        const int j0 = c * NTG * VW + lt * VW;
+        if (TAIL && j0 >= n) continue;
+        V q = (V)(T(0));
+#pragma unroll
+        for (int g = 0; g < RG; ++g)
+            if (g < groups) q += L.q[g][c][lt];
+        *(V *)(qrow + j0) = q;
+    }
+}
+
 template <typename T, int D>
 hipError_t launch_flow(const SweepArgs<T> &a, int threads, int nb, bool tail, hipStream_t st) {
-#define HAP_LAUNCH_FLOW(NTG, RG, ONE)                                                                                  \
-    do {                                                                                                               \
-        if (tail)                                                                                                      \
-            hipLaunchKernelGGL((sweep_flow_kernel<T, NTG, 4, RG, true, D, ONE>), dim3(nb), dim3(NTG * RG), 0, st, a);  \
-        else                                                                                                           \
-            hipLaunchKernelGGL((sweep_flow_kernel<T, NTG, 4, RG, false, D, ONE>), dim3(nb), dim3(NTG * RG), 0, st, a); \
-        return hipGetLastError();                                                                                      \
+#define HAP_LAUNCH_FLOW(KERNEL, NTG, RG)                                                                 \
+    do {                                                                                                 \
+        if (tail)                                                                                        \
+            hipLaunchKernelGGL((KERNEL<T, NTG, 4, RG, true, D>), dim3(nb), dim3(NTG * RG), 0, st, a);    \
+        else                                                                                             \
+            hipLaunchKernelGGL((KERNEL<T, NTG, 4, RG, false, D>), dim3(nb), dim3(NTG * RG), 0, st, a);   \
+        return hipGetLastError();                                                                        \
     } while (0)
     // 1024 threads (128 registers each), as many rows in flight as fit them; rows of one wave: four, the
     // most a workgroup has at these lengths by default
-    const bool one = a.rb <= (threads == 64 ? 4 : 8);
-    if (threads == 64 && one) HAP_LAUNCH_FLOW(64, 4, true);
-    if (threads == 64) HAP_LAUNCH_FLOW(64, 4, false);
-    if (threads == 128 && one) HAP_LAUNCH_FLOW(128, 8, true);
-    if (threads == 128) HAP_LAUNCH_FLOW(128, 8, false);
-    if (threads == 256) HAP_LAUNCH_FLOW(256, 4, false);
-    if (threads == 512) HAP_LAUNCH_FLOW(512, 2, false);
+    if constexpr (D <= 0) {
+        if (threads == 64 && a.rb <= 4) HAP_LAUNCH_FLOW(sweep_flow_one_kernel, 64, 4);
+        if (threads == 128 && a.rb <= 8) HAP_LAUNCH_FLOW(sweep_flow_one_kernel, 128, 8);
+    }
+    if (threads == 64) HAP_LAUNCH_FLOW(sweep_flow_kernel, 64, 4);
+    if (threads == 128) HAP_LAUNCH_FLOW(sweep_flow_kernel, 128, 8);
+    if (threads == 256) HAP_LAUNCH_FLOW(sweep_flow_kernel, 256, 4);
+    if (threads == 512) HAP_LAUNCH_FLOW(sweep_flow_kernel, 512, 2);
 #undef HAP_LAUNCH_FLOW
     return hipErrorInvalidValue;
 }
