@@ -863,26 +863,42 @@ hap_status hap_iterate(hap_ctx *c, int32_t max_iters, int32_t stable_iters, int3
             }
         }
     }
-    HIP_TRY(hipMemcpyAsync(&hs, c->ds, sizeof(DevState), hipMemcpyDeviceToHost, c->stream), c);
-    HIP_TRY(hipStreamSynchronize(c->stream), c);
-    if (hs.pair_abort) {
+    auto read_state = [&]() -> hap_status {
+        HIP_TRY(hipMemcpyAsync(&hs, c->ds, sizeof(DevState), hipMemcpyDeviceToHost, c->stream), c);
+        HIP_TRY(hipStreamSynchronize(c->stream), c);
+        return HAP_OK;
+    };
+    auto aborted = [&]() -> hap_status {
+        if (!hs.pair_abort) return HAP_OK;
         c->failed = true;
         return fail_arg("hap_iterate: the paired row pass gave up waiting for a partner workgroup (part of the "
                         "device was busy); the state is not valid",
                         HAP_E_HIP);
+    };
+    hap_status rs = HAP_OK;
+    // With the stop rule the state of the last chunk has been read; without it the iteration count is known,
+    // and the state is read once, after the labels (only no sweep at all leaves it to be read here).
+    const bool counted = stable_iters == 0 && max_iters > 0;
+    if (counted)
+        c->t_host += max_iters;
+    else {
+        if (max_iters == 0 || stable_iters == 0) rs = read_state();
+        if (rs == HAP_OK) rs = aborted();
+        if (rs != HAP_OK) return rs;
+        c->t_host = hs.t;
     }
-    c->t_host = hs.t;
-    int conv = 0, done_iter = hs.t;
-    if (stopped || hs.done) {
+    int conv = 0, done_iter = c->t_host;
+    if (!counted && (stopped || hs.done)) {
         // labels of the stop iteration are the last ones the row pass recorded
         HIP_TRY(hipMemcpyAsync(c->Efinal, c->E, (size_t)c->ldw * 4 * c->L, hipMemcpyDeviceToDevice, c->stream), c);
         conv = 1;
         done_iter = hs.stop_iter;
     } else {
-        hap_status s = (c->dtype == HAP_F32) ? finalize_labels<float>(c) : finalize_labels<double>(c);
-        if (s != HAP_OK) return s;
-        HIP_TRY(hipMemcpyAsync(&hs, c->ds, sizeof(DevState), hipMemcpyDeviceToHost, c->stream), c);
-        HIP_TRY(hipStreamSynchronize(c->stream), c);
+        rs = (c->dtype == HAP_F32) ? finalize_labels<float>(c) : finalize_labels<double>(c);
+        if (rs == HAP_OK) rs = read_state();
+        if (rs == HAP_OK) rs = aborted();
+        if (rs != HAP_OK) return rs;
+        c->t_host = done_iter = hs.t;
         if (stable_iters > 0 && c->t_host >= 2) {
             // stable count after comparing e^t with e^{t-1}; hs.stable is the count after iteration t-1
             const int st_after = hs.final_changed ? 0 : hs.stable + 1;
@@ -905,9 +921,10 @@ hap_status hap_exemplars(hap_ctx *c, int32_t level, int32_t *labels, int32_t *n_
         c->labels_ready = true;
     }
     const int32_t *src = c->Efinal + (size_t)c->ldw * level;
-    if (labels) HIP_TRY(hipMemcpyAsync(labels, src, (size_t)c->n * 4, hipMemcpyDeviceToDevice, c->stream), c);
+    if (labels && !n_exemplars)
+        HIP_TRY(hipMemcpyAsync(labels, src, (size_t)c->n * 4, hipMemcpyDeviceToDevice, c->stream), c);
     if (n_exemplars) {
-        HIP_TRY(hap::launch_count_distinct(src, (int)c->rows, (int)c->n, c->mark, c->count, c->stream), c);
+        HIP_TRY(hap::launch_count_distinct(src, (int)c->rows, (int)c->n, labels, c->count, c->stream), c);
         HIP_TRY(hipMemcpyAsync(n_exemplars, c->count, 4, hipMemcpyDeviceToHost, c->stream), c);
         HIP_TRY(hipStreamSynchronize(c->stream), c);
     }
@@ -937,18 +954,13 @@ hap_status hap_net_similarity(hap_ctx *c, int32_t level, const void *X, int64_t 
 
 hap_status hap_preference(hap_ctx *c, double *out) {
     if (!c || !out) return fail_arg("hap_preference: null pointer");
-    for (int l = 0; l < c->L; ++l) {
-        const char *src = c->pref + (size_t)c->ldw * c->esz * l;
-        if (c->dtype == HAP_F32) {
-            float f;
-            HIP_TRY(hipMemcpyAsync(&f, src, 4, hipMemcpyDeviceToHost, c->stream), c);
-            HIP_TRY(hipStreamSynchronize(c->stream), c);
-            out[l] = f;
-        } else {
-            HIP_TRY(hipMemcpyAsync(&out[l], src, 8, hipMemcpyDeviceToHost, c->stream), c);
-            HIP_TRY(hipStreamSynchronize(c->stream), c);
-        }
-    }
+    // the first element of every level's vector
+    double buf[64];
+    HIP_TRY(hipMemcpy2DAsync(buf, c->esz, c->pref, (size_t)c->ldw * c->esz, c->esz, (size_t)c->L, hipMemcpyDeviceToHost,
+                             c->stream),
+            c);
+    HIP_TRY(hipStreamSynchronize(c->stream), c);
+    for (int l = 0; l < c->L; ++l) out[l] = c->dtype == HAP_F32 ? (double)((const float *)buf)[l] : buf[l];
     return HAP_OK;
 }
 

@@ -170,8 +170,9 @@ hipError_t launch_colsum_levels(const FusedArgs<float> &f, const LevelPtrs<float
 template <typename T>
 hipError_t launch_alpha_pad(T *A, int64_t rows, int n, int64_t ldw, hipStream_t st);
 
-// Number of distinct values among labels[0, rows), every value in [0, n) (mark: int32 [n]).
-hipError_t launch_count_distinct(const int32_t *labels, int rows, int n, int32_t *mark, int32_t *out, hipStream_t st);
+// Number of distinct values in [0, n) among labels[0, rows); copy (or nullptr) receives labels[0, n).
+// n <= 65536.
+hipError_t launch_count_distinct(const int32_t *labels, int rows, int n, int32_t *copy, int32_t *out, hipStream_t st);
 hipError_t launch_net_similarity(const void *S, int64_t lds, int dtype, const void *pref_base,
                                  int64_t ldw, const int32_t *Efinal_base, int n, int levels,
                                  const void *X, int64_t d, int64_t ldx, int x_dtype, double *out,

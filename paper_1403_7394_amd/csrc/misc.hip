@@ -16,28 +16,35 @@ __global__ void fill_pref_kernel(T *pref, int64_t ldw, int n, int levels, const 
     }
 }
 
-__global__ void zero_i32(int32_t *p, int n) {
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) p[k] = 0;
-}
-
-__global__ void mark_labels(const int32_t *labels, int rows, int n, int32_t *mark) {
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < rows; k += gridDim.x * blockDim.x) {
-        const int e = labels[k];
-        if (e >= 0 && e < n) mark[e] = 1;
-    }
-}
-
-__global__ __launch_bounds__(1024) void sum_marks(const int32_t *mark, int n, int32_t *out) {
-    __shared__ int part[1024];
-    int acc = 0;
-    for (int k = threadIdx.x; k < n; k += 1024) acc += mark[k];
-    part[threadIdx.x] = acc;
+// Number of distinct values in [0, n) among labels[0, rows), and (copy != nullptr) labels[0, n) copied.
+// One workgroup with a bit per point in LDS: a launch, where clearing, marking and summing an array of
+// marks took three and the copy another.
+constexpr int kMaxLabels = 65536;   // the most points a context holds
+__global__ __launch_bounds__(1024) void count_labels_kernel(const int32_t *__restrict__ labels, int rows, int n,
+                                                            int32_t *__restrict__ copy, int32_t *__restrict__ out) {
+    __shared__ unsigned int bits[kMaxLabels / 32];
+    __shared__ int part[16];
+    const int tid = threadIdx.x;
+    for (int w = tid; w < (n + 31) / 32; w += 1024) bits[w] = 0u;
     __syncthreads();
-    for (int off = 512; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) part[threadIdx.x] += part[threadIdx.x + off];
-        __syncthreads();
+#pragma unroll 8
+    for (int k = tid; k < n; k += 1024) {
+        const int e = labels[k];
+        if (copy) copy[k] = e;
+        if (k < rows && e >= 0 && e < n) atomicOr(&bits[e >> 5], 1u << (e & 31));
     }
-    if (threadIdx.x == 0) *out = part[0];
+    __syncthreads();
+    int acc = 0;
+    for (int w = tid; w < (n + 31) / 32; w += 1024) acc += __popc(bits[w]);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if ((tid & 63) == 0) part[tid >> 6] = acc;
+    __syncthreads();
+    if (tid == 0) {
+        int s = 0;
+        for (int w = 0; w < 16; ++w) s += part[w];
+        *out = s;
+    }
 }
 
 // NS^l = sum_i s^l_{i,e_i}, s^l_ii = p^l_i, in FP64; out[l] per level and out[levels] the total.
@@ -203,11 +210,9 @@ hipError_t launch_fill_pref(void *pref_base, int64_t ldw, int n, int levels, int
     return hipGetLastError();
 }
 
-hipError_t launch_count_distinct(const int32_t *labels, int rows, int n, int32_t *mark, int32_t *out, hipStream_t st) {
-    const int grid = (n + 255) / 256;
-    hipLaunchKernelGGL(zero_i32, dim3(grid), dim3(256), 0, st, mark, n);
-    hipLaunchKernelGGL(mark_labels, dim3((rows + 255) / 256), dim3(256), 0, st, labels, rows, n, mark);
-    hipLaunchKernelGGL(sum_marks, dim3(1), dim3(1024), 0, st, mark, n, out);
+hipError_t launch_count_distinct(const int32_t *labels, int rows, int n, int32_t *copy, int32_t *out, hipStream_t st) {
+    if (n > kMaxLabels) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(count_labels_kernel, dim3(1), dim3(1024), 0, st, labels, rows, n, copy, out);
     return hipGetLastError();
 }
 

@@ -1010,11 +1010,15 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinArgs<T> a) {
     const T d_i = has_d ? a.delta[i] : zero;
     T mx = neg_inf<T>(), cv = neg_inf<T>();
     int ck = INT_MAX;
+#pragma unroll 4
     for (int j0 = tid * VW; j0 < n; j0 += NT * VW) {
-        V sv = *(const V *)(Srow + j0);
-        if (has_d) sv = sv + d_i;
-        const V rv = *(const V *)(Rrow + j0);
-        V av = *(const V *)(Arow + j0);
+        V sv = (V)(zero);
+        if (a.phi_out) {   // s enters phi only
+            sv = *(const V *)(Srow + j0);
+            if (has_d) sv = sv + d_i;
+        }
+        const V rv = __builtin_nontemporal_load((const V *)(Rrow + j0));
+        V av = __builtin_nontemporal_load((const V *)(Arow + j0));
         const V bv = *(const V *)(a.B + j0);
 #pragma unroll
         for (int v = 0; v < VW; ++v) {
