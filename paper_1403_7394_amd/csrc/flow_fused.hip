@@ -1,5 +1,5 @@
 // The fused all-level row pass of the MapReduce schedule (see fused.hip) with several rows of a
-// workgroup in flight (see flowpass.h): rows of up to 4096 FP32 columns, up to 64 rows per workgroup.
+// workgroup in flight (see flowpass.h): rows of up to 4096 FP32 columns, one to 64 rows per workgroup.
 // A group keeps its row of S in registers over the levels; the levels' availability bases and column
 // sums live in LDS (2 x 4 levels x 16 KB at most).  The one-row pass has four waves per CU at 3000
 // points and waits out every (row, level) item's loads and barrier: 147 us a sweep of three levels

@@ -275,7 +275,7 @@ hipError_t launch_sweep_fused(const FusedArgs<float> &a, const Launch &lc, hipSt
     } while (0)
     // several rows in flight wherever the bases and column sums of four levels fit the LDS (rows of up to
     // 4096 columns) and a workgroup's rows are staged at once
-    if (lc.threads < 512 && a.rb > 1 && a.rb <= kWin) return launch_fused_flow(a, lc.threads, nb, tail, st);
+    if (lc.threads < 512 && a.rb <= kWin) return launch_fused_flow(a, lc.threads, nb, tail, st);
     switch (lc.threads) {
         case 64: HAP_LAUNCH_FUSED(64); break;
         case 128: HAP_LAUNCH_FUSED(128); break;

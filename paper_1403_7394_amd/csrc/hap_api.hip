@@ -406,14 +406,14 @@ hap_status run_sweeps(hap_ctx *c, int count, int K) {
                 HIP_TRY(prof_mark(c, 0, false), c);
                 HIP_TRY(hap::launch_sweep_fused(fa, c->lc, c->stream), c);
                 HIP_TRY(prof_mark(c, 0, true), c);
-                if (c->lc.ordered || c->prof) {
+                if (c->prof) {
                     // one launch per level, which hap_profile counts
                     for (int l = 0; l < L; ++l) {
                         const hap_status s = col(l, (T *)fa.Qpart[l], false);
                         if (s != HAP_OK) return s;
                     }
                 } else {
-                    HIP_TRY(hap::launch_colsum_levels(fa, fl, nb, K, c->stream), c);
+                    HIP_TRY(hap::launch_colsum_levels(fa, fl, nb, K, c->lc.ordered, c->stream), c);
                 }
                 continue;
             }

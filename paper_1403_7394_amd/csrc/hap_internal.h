@@ -161,12 +161,12 @@ struct FusedArgs {
 };
 bool fused_supported(int threads, int chunks, int levels);
 hipError_t launch_sweep_fused(const FusedArgs<float> &a, const Launch &lc, hipStream_t st);
-// Its form with several rows of a workgroup in flight (64, 128 or 256 threads per row, 2..64 rows per
+// Its form with several rows of a workgroup in flight (64, 128 or 256 threads per row, up to 64 rows per
 // workgroup).
 hipError_t launch_fused_flow(const FusedArgs<float> &a, int threads, int nb, bool tail, hipStream_t st);
-// Column sums, availability bases and stop rule of every level after the fused pass (unordered partials,
-// nb per level).
-hipError_t launch_colsum_levels(const FusedArgs<float> &f, const LevelPtrs<float> *lv, int nb, int K, hipStream_t st);
+// Column sums, availability bases and stop rule of every level after the fused pass (nb partials per level).
+hipError_t launch_colsum_levels(const FusedArgs<float> &f, const LevelPtrs<float> *lv, int nb, int K, bool ordered,
+                                hipStream_t st);
 template <typename T>
 hipError_t launch_alpha_pad(T *A, int64_t rows, int n, int64_t ldw, hipStream_t st);
 

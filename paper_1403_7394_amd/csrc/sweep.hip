@@ -927,7 +927,7 @@ __global__ __launch_bounds__(64 * kColVecs) void colsum_levels_kernel(ColLevels 
 // thread per column vector that loads sixteen rows ahead waits a memory latency per sixteen rows: 12.0
 // us at 300 FP64 points against 5.0 us.)
 template <typename T>
-__global__ __launch_bounds__(256) void colsum_ordered_kernel(ColArgs<T> a) {
+__device__ __forceinline__ void colsum_ordered_body(const ColArgs<T> &a) {
 #pragma clang fp contract(off)
     constexpr int CB = 16, RT = 256, PER = RT / 16;
     __shared__ T tile[2][RT][CB];
@@ -962,6 +962,14 @@ __global__ __launch_bounds__(256) void colsum_ordered_kernel(ColArgs<T> a) {
     if (skip) return;
     if (tid < CB && j < n) col_after(a, j, acc, cv, bd, ph);
     if (a.last && blockIdx.x == 0 && tid == 0) col_stop_rule(a);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void colsum_ordered_kernel(ColArgs<T> a) {
+    colsum_ordered_body<T>(a);
+}
+__global__ __launch_bounds__(256) void colsum_ordered_levels_kernel(ColLevels a) {
+    colsum_ordered_body<float>(a.level[blockIdx.y]);
 }
 
 // alpha^{l,t} materialised on the fly from A = alpha^{t-1}, R = rho^t (nothing in the
@@ -1321,7 +1329,8 @@ hipError_t launch_colsum(const T *Qpart, int64_t ldw, int nb, int n, const Level
     return hipGetLastError();
 }
 
-hipError_t launch_colsum_levels(const FusedArgs<float> &f, const LevelPtrs<float> *lv, int nb, int K, hipStream_t st) {
+hipError_t launch_colsum_levels(const FusedArgs<float> &f, const LevelPtrs<float> *lv, int nb, int K, bool ordered,
+                                hipStream_t st) {
     ColLevels c{};
     for (int l = 0; l < f.L; ++l) {
         const bool top = l == f.L - 1;
@@ -1335,8 +1344,12 @@ hipError_t launch_colsum_levels(const FusedArgs<float> &f, const LevelPtrs<float
             a.phi_own = lv[l].phi;
         }
     }
-    const dim3 grid((unsigned)((f.n + kColVecs * 4 - 1) / (kColVecs * 4)), (unsigned)f.L);
-    hipLaunchKernelGGL(colsum_levels_kernel, grid, dim3(64 * kColVecs), 0, st, c);
+    const int per = ordered ? 16 : kColVecs * 4;
+    const dim3 grid((unsigned)((f.n + per - 1) / per), (unsigned)f.L);
+    if (ordered)
+        hipLaunchKernelGGL(colsum_ordered_levels_kernel, grid, dim3(256), 0, st, c);
+    else
+        hipLaunchKernelGGL(colsum_levels_kernel, grid, dim3(64 * kColVecs), 0, st, c);
     return hipGetLastError();
 }
 

@@ -54,7 +54,7 @@ def test_equals_the_streaming_pass(hap_gpu, n, threads, rb, form):
             assert torch.equal(torch.nan_to_num(x[k], nan=7e30), torch.nan_to_num(y[k], nan=7e30)), (form, k)
 
 
-@pytest.mark.parametrize("n,threads,rb", [s for s in SHAPES if s[1] < 512])
+@pytest.mark.parametrize("n,threads,rb", [s for s in SHAPES if s[1] < 512] + [(2, 64, 1), (255, 64, 1), (300, 64, 1), (513, 128, 1), (1100, 256, 1)])
 @pytest.mark.parametrize("levels", [2, 4])
 def test_fused_levels_equal_the_per_level_passes(hap_gpu, n, threads, rb, levels):
     """The MapReduce schedule's all-level pass with several rows in flight."""
