@@ -50,7 +50,7 @@ struct hap_ctx {
     char *R = nullptr, *A = nullptr, *pref = nullptr, *Q = nullptr, *phi = nullptr, *tau = nullptr, *C = nullptr,
          *B = nullptr, *delta = nullptr;
     double kappa = 0.0;           // Eq. 2.7 weight (0: the update is off)
-    int32_t *E = nullptr, *Efinal = nullptr, *mark = nullptr, *count = nullptr;
+    int32_t *E = nullptr, *Efinal = nullptr, *count = nullptr;
     char *Qpart = nullptr;        // column partials of up to nb_cap workgroups (in the workspace)
     // column partials of launches with more than nb_cap workgroups (for example one row per
     // workgroup at n > 2048): allocated by the library when such a launch is set
@@ -99,7 +99,7 @@ constexpr int64_t kMaxPairs = 2048;   // pairs of the paired row pass's largest 
 inline size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
 struct Layout {
-    size_t R, A, pref, Q, phi, tau, C, B, delta, E, Efinal, mark, count, Qpart, ds, dbl, sel, total;
+    size_t R, A, pref, Q, phi, tau, C, B, delta, E, Efinal, count, Qpart, ds, dbl, sel, total;
     int64_t ldw;
     int nb_cap;
 };
@@ -127,7 +127,6 @@ Layout make_layout(int64_t n, int L, size_t esz) {
     lo.delta = take(vec * L);
     lo.E = take((size_t)lo.ldw * 4 * L);
     lo.Efinal = take((size_t)lo.ldw * 4 * L);
-    lo.mark = take((size_t)lo.ldw * 4);
     lo.count = take(64);
     lo.Qpart = take((size_t)2 * lo.nb_cap * vec);   // two buffers (the MapReduce schedule alternates)
     lo.ds = take(sizeof(DevState));
@@ -331,6 +330,7 @@ hap_status run_sweeps(hap_ctx *c, int count, int K) {
     ex.ldx = c->ldx;
     ex.d = c->d;
     ex.rows = (int)c->rows;
+    ex.keep = c->kappa == 0.0 && (2 * (int64_t)L + 1) * c->rows * c->ldw * (int64_t)sizeof(T) <= ((int64_t)256 << 20);
     const bool kappa = c->kappa != 0.0;
     auto row = [&](int l, T *qp) -> hap_status {
         LevelPtrs<T> lv = level_ptrs<T>(c, l);
@@ -781,7 +781,6 @@ hap_status hap_init(hap_ctx **out, const void *S, int64_t n, int64_t lds, int32_
     c->delta = base + lo.delta;
     c->E = (int32_t *)(base + lo.E);
     c->Efinal = (int32_t *)(base + lo.Efinal);
-    c->mark = (int32_t *)(base + lo.mark);
     c->count = (int32_t *)(base + lo.count);
     c->Qpart = base + lo.Qpart;
     c->ds = (DevState *)(base + lo.ds);

@@ -91,6 +91,7 @@ struct SweepExtra {
     uint64_t *pair_slots = nullptr;   // the paired row pass's exchange slots (kPairSlotWords per pair)
     uint64_t pair_wait = 0;           // wall-clock ticks one of its waits may take
     int pair_level = 0;               // the level this launch updates (part of the exchange tags)
+    bool keep = false;                // S and every level's rho and alpha fit the Infinity Cache together
 };
 // The paired row pass (FP32 rows of 32768 < n <= 65536, two workgroups per block of rows):
 // exchange slots in device memory, 20 words per pair, initialised to all ones (a tag no row

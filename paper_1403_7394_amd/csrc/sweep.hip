@@ -25,13 +25,13 @@
 //
 // Each workgroup owns a set of rows (by default, of G workgroups, workgroup g takes rows g,
 // g + G, g + 2G, ...; a contiguous block on request) and keeps its column partials in
-// registers (every thread owns the same columns for every row); the partials are summed in a
+// registers or LDS (every thread owns the same columns for every row); the partials are summed in a
 // fixed order by the epilogue, so results are deterministic.
 #include "rowpass.h"
 
 namespace hap {
 
-template <typename T, int NT, int NCH, bool TAIL, int D>
+template <typename T, int NT, int NCH, bool TAIL, int D, bool KEEP = false>
 __global__ __launch_bounds__(NT) void sweep_kernel(SweepArgs<T> a) {
 #pragma clang fp contract(off)
     using V = typename Vec<T>::type;
@@ -80,9 +80,9 @@ __global__ __launch_bounds__(NT) void sweep_kernel(SweepArgs<T> a) {
                                                           sh_ck, cp, lds);
     } else {
         if (first)
-            sweep_rows<T, NT, NCH, true, TAIL, D>(a, t, row0, row1, Bv, qv, sh_m1, sh_k1, sh_m2, sh_cv, sh_ck);
+            sweep_rows<T, NT, NCH, true, TAIL, D, KEEP>(a, t, row0, row1, Bv, qv, sh_m1, sh_k1, sh_m2, sh_cv, sh_ck);
         else
-            sweep_rows<T, NT, NCH, false, TAIL, D>(a, t, row0, row1, Bv, qv, sh_m1, sh_k1, sh_m2, sh_cv, sh_ck);
+            sweep_rows<T, NT, NCH, false, TAIL, D, KEEP>(a, t, row0, row1, Bv, qv, sh_m1, sh_k1, sh_m2, sh_cv, sh_ck);
     }
 
     T *qrow = a.Qpart + (int64_t)blockIdx.x * ldw;
@@ -399,7 +399,7 @@ __device__ __forceinline__ void stream_rows_unpipelined(const SweepArgs<T> &a, c
 }
 
 // Row pass for rows of up to NT*NCH*4 FP32 columns that do not fit the register-resident pass
-// (16384 < n <= 32768 at 512 threads and 16 chunks): the row's S and rho are held in registers
+// (8192 < n <= 32768 at 512 threads and 6, 8 or 16 chunks): the row's S and rho are held in registers
 // from phase 1 to phase 2 (128 registers), so phase 2 reads nothing from memory; alpha is
 // finished and stored in phase 1, the column bases B are read per chunk, and the column
 // partials live in LDS.  Phase 1's loads run one chunk ahead of the arithmetic, and the next
@@ -925,7 +925,7 @@ __global__ __launch_bounds__(64 * kColVecs) void colsum_levels_kernel(ColLevels 
 // sum).  Sixteen columns per workgroup: 256 threads bring 256 partial rows at a time into LDS, the
 // next 256 on their way to registers meanwhile, and sixteen threads add them one after another.  (One
 // thread per column vector that loads sixteen rows ahead waits a memory latency per sixteen rows: 12.0
-// us at 300 FP64 points against 5.0 us.)
+// us at 300 FP64 points against 5.4 us.)
 template <typename T>
 __device__ __forceinline__ void colsum_ordered_body(const ColArgs<T> &a) {
 #pragma clang fp contract(off)
@@ -1160,7 +1160,7 @@ hipError_t launch_resident(const SweepArgs<T> &a, const Launch &lc, int nb, bool
 
 // The row pass with several rows of a workgroup in flight (flowpass.h): FP32, four chunks per thread and
 // from two to kWin rows per workgroup (their scalars are staged once).  Against the one-row pass, per
-// level with its column sums: 788 points 19.8 -> 11.6 us, 2000 points 35.8 -> 20.6, 3000 points 53.2 ->
+// level with its column sums: 788 points 19.8 -> 10.0 us, 2000 points 35.8 -> 20.1, 3000 points 53.2 ->
 // 36.8, 6000 points 148 -> 136, in points mode 57 -> 34 (3000) and 135 -> 115 (6000).  Rows of 8192
 // columns that read S are bound by memory either way and stay with the one-row pass, whose
 // prefetched row covers the latency without LDS traffic (240 us against 246); so do FP64 rows (4000
@@ -1280,6 +1280,15 @@ hipError_t launch_sweep_level(const T *S, int64_t lds, const LevelPtrs<T> &lv, T
         }
     }
     if (ex.delta != nullptr) return launch_resident<T, -1>(a, lc, nb, tail, st);
+    // FP64 rows of 2048 < n < 4096 with a state of at most 256 MB, the Infinity Cache: cached accesses.  Per level
+    // with its column sums, 2500 points 58.3 -> 53.5 us with two levels (250 MB), 3000 points 75.4 -> 66.1 with one
+    // (216 MB); past 256 MB they lose (3000 points with two levels, 360 MB, 75.6 -> 76.6; 4000 points 124 -> 130).
+    if constexpr (sizeof(T) == 8) {
+        if (X == nullptr && ex.keep && lc.threads == 512 && lc.chunks == 4 && tail) {
+            hipLaunchKernelGGL((sweep_kernel<T, 512, 4, true, 0, true>), dim3(nb), dim3(512), 0, st, a);
+            return hipGetLastError();
+        }
+    }
     if (X == nullptr) return launch_resident<T, 0>(a, lc, nb, tail, st);
     if constexpr (sizeof(T) == 4) {
         if (d == 2) return launch_resident<T, 2>(a, lc, nb, tail, st);
