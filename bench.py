@@ -42,6 +42,7 @@ TRAFFIC_FILES = {True: os.path.join(ROOT, "profiles", "row_pass_traffic_plain819
                  False: os.path.join(ROOT, "profiles", "row_pass_traffic_plain8192.json")}
 SWEEP_SRC = os.path.join(ROOT, "paper_1403_7394_amd", "csrc", "sweep.hip")
 ROWPASS_SRC = os.path.join(ROOT, "paper_1403_7394_amd", "csrc", "rowpass.h")
+FLOWPASS_SRC = os.path.join(ROOT, "paper_1403_7394_amd", "csrc", "flowpass.h")
 PROF_EVERY = 8
 
 
@@ -60,7 +61,8 @@ def measured_traffic(points: bool, first_launches: int, steady_launches: int):
     except (OSError, ValueError):
         return None
     if (t.get("sweep_source_sha256_16") != _hash16(SWEEP_SRC)
-            or t.get("rowpass_source_sha256_16") != _hash16(ROWPASS_SRC)):
+            or t.get("rowpass_source_sha256_16") != _hash16(ROWPASS_SRC)
+            or t.get("flowpass_source_sha256_16") != _hash16(FLOWPASS_SRC)):
         return None
     total = first_launches + steady_launches
     if total == 0:
@@ -836,7 +838,7 @@ def main() -> int:
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
             "traffic": traffic,
-            "kernel": ("row pass (sweep_kernel, points mode)" if use_points else
+            "kernel": ("row pass (sweep_flow_kernel, points mode)" if use_points else
                        "row pass (sweep_kernel, S read, Eq. 2.7 row offsets)" if args.kappa else
                        f"fused row pass of all {L} levels (sweep_fused_kernel, S read once)" if fused else
                        "row pass (sweep_kernel, S read)"),

@@ -269,8 +269,9 @@ HAP_API hap_status hap_similarity_offsets(hap_ctx *ctx, int32_t level, void *del
  * library's choice for that field.  flags (a bit set; -1 keeps the current
  * choices): HAP_LAUNCH_STREAM selects a row pass for long rows: with 1024 threads and 1
  * to 16 chunks the streaming pass (the row is read again from the caches in its second
- * phase), with 512 threads and 16 chunks (FP32 only, n <= 32768, the default for
- * 16384 < n <= 32768) the held-row pass (the row's s and rho stay in registers between
+ * phase; the default for 8192 < n <= 16384 in FP32 is reported as this shape and run by the
+ * held-row pass, which gives the same results faster), with 512 threads and 16 chunks (FP32 only,
+ * n <= 32768, the default for 16384 < n <= 32768) the held-row pass (the row's s and rho stay in registers between
  * the phases), with 512 (or 64) threads and 32 chunks the paired pass (FP32 only,
  * threads*64 < n <= threads*128; the default for 32768 < n <= 65536 with 128 pairs): two
  * workgroups share each block of rows_per_block rows, each holding half of every row as
@@ -400,7 +401,8 @@ HAP_API hap_status hap_batch_run(hap_batch *batch, const void *X, double damping
  * (>= 1) and the row groups per workgroup.  With G row groups a workgroup sweeps G rows of
  * its problem at once (each group owning NT/G threads); the rows' column-sum contributions
  * are still added in row order, so every shape computes the same values bit for bit.
- * (threads, row_groups) is one of (256, 1), (512, 1), (512, 2), (512, 4), (1024, 4); any
+ * With four row groups, problems of up to 1024 points are swept by one wave per row, NT/64 rows at
+ * once.  (threads, row_groups) is one of (256, 1), (512, 1), (512, 2), (512, 4), (1024, 4); any
  * other pair is rejected with HAP_E_ARG and changes nothing.  0 keeps the current value.
  * While some problem is split, the launch uses at most as many workgroups as fit the device
  * at once.  For the autotuner. */
@@ -508,8 +510,9 @@ HAP_API hap_status hap_iterate_warm_judged(hap_ctx *ctx, const float *Y, int64_t
  * W2 (hidden x hidden), b2, W3 (hidden x n_out), b3.  precision HAP_F32 multiplies FP32
  * operands, HAP_BF16 rounds both operands of every product to BF16 (nearest even); both
  * accumulate in FP32 on the matrix cores.  X, Y, T are device FP32 row-major with the given
- * row strides.  The workspace (device, 256-byte aligned, caller-owned) holds the activations
- * of `rows` rows: hap_mlp_workspace_size bytes.  Nothing synchronises the stream.
+ * row strides.  The workspace (device, 256-byte aligned, caller-owned) holds the activations of
+ * `rows` rows, or what the fused kernels of small networks (n_in <= 32, hidden <= 256,
+ * n_out <= 16) keep instead: hap_mlp_workspace_size bytes.  Nothing synchronises the stream.
  */
 HAP_API int64_t hap_mlp_param_count(int32_t n_in, int32_t hidden, int32_t n_out); /* -1 for bad sizes */
 HAP_API hap_status hap_mlp_workspace_size(int32_t n_in, int32_t hidden, int32_t n_out, int64_t rows, size_t *bytes);
