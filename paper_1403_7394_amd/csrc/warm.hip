@@ -27,13 +27,15 @@ constexpr int kScales = 6;
 
 // One workgroup per row.  A first pass over the row takes the largest value of every four threads and the
 // sums; the sixteenth largest of these 64 maxima is at most the row's sixteenth largest value, so the
-// row's top 16 are among the few values that reach it, which a second pass collects in LDS and ranks by
-// counting.  Up to 256 NV vectors the row stays in registers between the passes (NV = 0: it is read
-// again).  (A sorted list of sixteen per lane costs an insertion of sixteen steps for nearly every
-// element: 358 us at 8192 FP32 points against 126 us here, 2.1 TB/s.  What bounds it now is the FP64
-// arithmetic of the sums, about 20 operations per element.)
+// row's top 16 are among the values that reach it, which a second pass collects in LDS and ranks by
+// counting.  Usually they are a few dozen; where the nearest columns fall into few of the 64 groups, or are
+// equal by the hundred, they can be thousands, and the bound is raised from a sample of them.
+// Up to 256 NV vectors the row stays in registers between the passes (NV = 0: it is read again).
+// 8192 FP32 points, the whole call: 124 us with points in random order, 281 us in a cyclic one (runs of 16
+// columns in 1024; sixteen more reads of every such row took 1334 us), 234 us with four places for all
+// points; a sorted list of sixteen per lane takes 387, 308 and 345 us.
 constexpr int kFeatThreads = 256;
-constexpr int kFeatCap = 512;   // collected values; more (equal values without end) are extracted one by one
+constexpr int kFeatCap = 512;   // collected values; more of them: the bound is raised until they fit
 
 template <typename T, int NV>
 __global__ __launch_bounds__(kFeatThreads) void warm_features_kernel(const T *__restrict__ S, int64_t lds,
@@ -45,20 +47,21 @@ __global__ __launch_bounds__(kFeatThreads) void warm_features_kernel(const T *__
     using V = typename Vec<T>::type;
     constexpr int VW = Vec<T>::N, NT = kFeatThreads, NW = NT / 64, NG = NT / 4;
     __shared__ __attribute__((aligned(16))) T maxima[NG];
-    __shared__ T cv[kFeatCap];
-    __shared__ int cj[kFeatCap];
+    __shared__ __attribute__((aligned(16))) T cv[kFeatCap];
+    __shared__ __attribute__((aligned(16))) int cj[kFeatCap];
     __shared__ T top_v[kTop];
     __shared__ int top_j[kTop];
     __shared__ double part[NW][kScales + 1];
     __shared__ int pcnt[NW];
     __shared__ T bound;
+    __shared__ int bound_j;
     __shared__ int collected;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     const int i = blockIdx.x;
     const T *row = S + (int64_t)i * lds;
     const T p = pref[i];
     const double pd = (double)p, a = fabs(pd);
-    const T ninf = neg_inf<T>();
+    const T ninf = neg_inf<T>(), nan = (T)__builtin_nanf("");
     double thr[kScales], D[kScales], sum = 0.0;
 #pragma unroll
     for (int m = 0; m < kScales; ++m) {
@@ -67,15 +70,15 @@ __global__ __launch_bounds__(kFeatThreads) void warm_features_kernel(const T *__
     }
     int cnt = 0;
     T mx = ninf;
-    // the diagonal and the columns past n count as -inf; only a wave whose vectors hold one of them
-    // looks for it
+    // the diagonal and the columns past n become NaN, which no comparison takes; only a wave whose vectors
+    // hold one of them looks for it
     auto first = [&](V &v, int w0, int j0) {
         V vd0 = v;
         if ((unsigned)(i - w0) < (unsigned)(64 * VW) || w0 + 64 * VW > n) {
 #pragma unroll
             for (int e = 0; e < VW; ++e) {
                 const bool out = j0 + e >= n || j0 + e == i;
-                v[e] = out ? ninf : v[e];
+                v[e] = out ? nan : v[e];
                 vd0[e] = out ? T(0) : vd0[e];
             }
         }
@@ -146,93 +149,107 @@ __global__ __launch_bounds__(kFeatThreads) void warm_features_kernel(const T *__
         if (rank == kTop - 1) bound = mine;
     }
     __syncthreads();
-    const T lo = bound;
-    auto second = [&](const V &v, int j0) {
-        T vm = v[0];
-#pragma unroll
-        for (int e = 1; e < VW; ++e) vm = fmax(vm, v[e]);
-        if (!(vm >= lo)) return;
+    T lo = bound;
+    int lo_j = INT_MAX;   // of the values equal to lo, the columns up to this one
+    // The list takes what reaches the bound: a wave counts its own and reserves their places at once.
+    auto collect = [&](const V &v, int j0) {
+        bool take[VW];
+        unsigned long long who[VW], any = 0;
 #pragma unroll
         for (int e = 0; e < VW; ++e) {
             const int j = j0 + e;
-            if (v[e] >= lo && j < n && j != i) {
-                const int at = atomicAdd(&collected, 1);
-                if (at < kFeatCap) {
-                    cv[at] = v[e];
-                    cj[at] = j;
+            take[e] = (v[e] > lo) | ((v[e] == lo) & (j <= lo_j));
+            if constexpr (NV == 0) take[e] = take[e] & (j < n) & (j != i);
+            any |= who[e] = __ballot(take[e]);
+        }
+        if (any == 0) return;
+        int total = 0, first_at = 0;
+#pragma unroll
+        for (int e = 0; e < VW; ++e) total += __popcll(who[e]);
+        if (lane == 0) first_at = atomicAdd(&collected, total);
+        first_at = __builtin_amdgcn_readfirstlane(first_at);
+#pragma unroll
+        for (int e = 0; e < VW; ++e) {
+            if (take[e]) {
+                const int at = first_at + __builtin_amdgcn_mbcnt_hi((unsigned)(who[e] >> 32),
+                                                                    __builtin_amdgcn_mbcnt_lo((unsigned)who[e], 0));
+                // past the end, a slot of 0 .. at: the list stays a sample of all that came
+                const int slot = at < kFeatCap ? at : (int)__umulhi((unsigned)at * 2654435761u, (unsigned)at + 1u);
+                if (slot < kFeatCap) {
+                    cv[slot] = v[e];
+                    cj[slot] = j0 + e;
                 }
             }
+            first_at += __popcll(who[e]);
         }
     };
-    if constexpr (NV > 0) {
+    auto collect_row = [&]() {
+        if constexpr (NV > 0) {
 #pragma unroll
-        for (int c = 0; c < NV; ++c) {
-            const int j0 = (c * NT + tid) * VW;
-            if (j0 < n) second(keep[c], j0);
-        }
-    } else {
-#pragma unroll 4
-        for (int j0 = tid * VW; j0 < n; j0 += NT * VW) second(*(const V *)(row + j0), j0);
-    }
-    __syncthreads();
-    const int avail = n - 1 < kTop ? n - 1 : kTop;
-    const int found = collected;
-    if (found <= kFeatCap) {
-        // values descending, equal values by column
-        for (int c = tid; c < found; c += NT) {
-            const T v = cv[c];
-            const int j = cj[c];
-            int better = 0;
-            for (int k = 0; k < found; ++k) better += (cv[k] > v || (cv[k] == v && cj[k] < j)) ? 1 : 0;
-            if (better < kTop) {
-                top_v[better] = v;
-                top_j[better] = j;
+            for (int c = 0; c < NV; ++c) {
+                const int j0 = (c * NT + tid) * VW;
+                if (c * NT * VW + wave0 < n) collect(keep[c], j0);
+            }
+        } else {
+            for (int w0 = wave0; w0 < n; w0 += 4 * NT * VW) {
+                V v[4];   // four loads in flight
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int j0 = w0 + u * NT * VW + lane * VW;
+                    v[u] = j0 < n ? *(const V *)(row + j0) : (V)(nan);
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) collect(v[u], w0 + u * NT * VW + lane * VW);
             }
         }
         __syncthreads();
-    } else {
-        // more equal values than the list holds: the largest (value, lowest column) after the last one
-        // taken, sixteen times
-        T last_v = pos_inf<T>();
-        int last_j = -1;
-        for (int r = 0; r < avail; ++r) {
-            T bv = ninf;
-            int bj = INT_MAX;
-            for (int j = tid; j < n; j += NT) {
-                const T v = row[j];
-                if (j == i || v > last_v || (v == last_v && j <= last_j)) continue;
-                if (v > bv || (v == bv && j < bj)) {
-                    bv = v;
-                    bj = j;
-                }
-            }
+        return collected;
+    };
+    // entries among the list's first m that come before (v, j): values descending, equal values by column
+    auto before = [&](T v, int j, int m) {
+        typedef int I4 __attribute__((ext_vector_type(4)));
+        int c = 0;
+#pragma unroll 2
+        for (int k = 0; k < m; k += 4) {
+            T o[4];
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                const T ov = __shfl_xor(bv, off, 64);
-                const int oj = __shfl_xor(bj, off, 64);
-                const bool take = ov > bv || (ov == bv && oj < bj);
-                bv = take ? ov : bv;
-                bj = take ? oj : bj;
-            }
-            if (lane == 0) {
-                cv[wid] = bv;
-                cj[wid] = bj;
-            }
-            __syncthreads();
-            for (int w = 0; w < NW; ++w)
-                if (cv[w] > bv || (cv[w] == bv && cj[w] < bj)) {
-                    bv = cv[w];
-                    bj = cj[w];
-                }
-            last_v = bv;
-            last_j = bj;
-            if (tid == 0) {
-                top_v[r] = bv;
-                top_j[r] = bj;
-            }
-            __syncthreads();
+            for (int e = 0; e < 4; e += VW) *(V *)&o[e] = *(const V *)&cv[k + e];
+            const I4 oj = *(const I4 *)&cj[k];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c += (int)((k + e < m) & ((o[e] > v) | ((o[e] == v) & (oj[e] < j))));
+        }
+        return c;
+    };
+    int found = collect_row();
+    // More than the list holds: the sixteenth best of 256 entries of the list is the next bound, which leaves
+    // out the other 240 at least and about 15 of 16 as a rule.
+    for (int left = n / (NT - kTop) + 1; found > kFeatCap && left > 0; --left) {
+        const int sj = cj[tid];
+        const T sv = row[sj];   // two entries may have been written to a slot: the column decides
+        cv[tid] = sv;
+        __syncthreads();
+        if (before(sv, sj, NT) == kTop - 1) {
+            bound = sv;
+            bound_j = sj;
+        }
+        if (tid == 0) collected = 0;
+        __syncthreads();
+        lo = bound;
+        lo_j = bound_j;
+        found = collect_row();
+    }
+    found = found < kFeatCap ? found : kFeatCap;
+    const int avail = n - 1 < kTop ? n - 1 : kTop;
+    for (int c = tid; c < found; c += NT) {
+        const T v = cv[c];
+        const int j = cj[c];
+        const int at = before(v, j, found);
+        if (at < kTop) {
+            top_v[at] = v;
+            top_j[at] = j;
         }
     }
+    __syncthreads();
     float *Fi = F + (int64_t)i * ldf;
     const int have = found < avail ? found : avail;   // fewer only where the row holds NaN
     if (tid < kTop) {
