@@ -269,10 +269,10 @@ HAP_API hap_status hap_similarity_offsets(hap_ctx *ctx, int32_t level, void *del
  * library's choice for that field.  flags (a bit set; -1 keeps the current
  * choices): HAP_LAUNCH_STREAM selects a row pass for long rows: with 1024 threads and 1
  * to 16 chunks the streaming pass (the row is read again from the caches in its second
- * phase; the default for 8192 < n <= 16384 in FP32 is reported as this shape and run by the
- * held-row pass, which gives the same results faster), with 512 threads and 16 chunks (FP32 only,
- * n <= 32768, the default for 16384 < n <= 32768) the held-row pass (the row's s and rho stay in registers between
- * the phases), with 512 (or 64) threads and 32 chunks the paired pass (FP32 only,
+ * phase), with 512 threads and 16 chunks (FP32 only, n <= 32768, the default for 16384 < n <= 32768) the
+ * held-row pass (the row's s and rho stay in registers between the phases; up to 16384 columns in six or eight
+ * chunks, with the same results), which also runs the streaming shape of 8192 < n <= 16384 FP32 columns with
+ * ceil(n / 4096) chunks, the default there (the same results faster; more chunks stream), with 512 (or 64) threads and 32 chunks the paired pass (FP32 only,
  * threads*64 < n <= threads*128; the default for 32768 < n <= 65536 with 128 pairs): two
  * workgroups share each block of rows_per_block rows, each holding half of every row as
  * the held-row pass does, and exchange the row maxima once per row through device memory;
@@ -299,11 +299,12 @@ HAP_API hap_status hap_similarity_offsets(hap_ctx *ctx, int32_t level, void *del
  * for a shape that does not fit.  For the autotuner and for comparisons.
  */
 enum { HAP_LAUNCH_STREAM = 2, HAP_LAUNCH_EAGER = 4, HAP_LAUNCH_UNFUSED = 8, HAP_LAUNCH_FUSED = 16,
-       HAP_LAUNCH_BLOCKS = 32 };
+       HAP_LAUNCH_BLOCKS = 32, HAP_LAUNCH_HELD = 64 };
 HAP_API hap_status hap_set_launch(hap_ctx *ctx, int32_t threads, int32_t chunks, int32_t rows_per_block,
                                   int32_t flags);
-/* The current shape and flags; flags also carries HAP_LAUNCH_FUSED (reported only, ignored by
- * hap_set_launch) when the sweeps will run the fused all-level pass. */
+/* The current shape and flags; flags also carries HAP_LAUNCH_FUSED when the sweeps will run the fused
+ * all-level pass and HAP_LAUNCH_HELD when they will run the held-row pass (both reported only, ignored by
+ * hap_set_launch).  Setting what was read changes nothing. */
 HAP_API hap_status hap_get_launch(hap_ctx *ctx, int32_t *threads, int32_t *chunks, int32_t *rows_per_block,
                                   int32_t *flags);
 

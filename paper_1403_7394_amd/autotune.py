@@ -87,16 +87,20 @@ def tune_sweep(h: "hap.Hap", sweeps: int = 3, use_cache: bool = True):
     so call it on a context whose iteration state may be consumed (or re-create it)."""
     esz = 4 if str(h.dtype).endswith("float32") else 8
     key = f"sweep:{_arch()}:n{_bucket(h.n)}:e{esz}"
+    # the shape in effect (the library's choice, as a rule) is one of those timed
+    shapes = [h.get_launch()]
+    shapes += [s for s in sweep_candidates(h.n, esz) if s != shapes[0]]
     if use_cache:
         hit = _load_cache().get(key)
-        if hit:
+        # a bucket holds sizes with different shapes: a stored one that is none of this size's is timed again
+        if hit and (hit[0], hit[1], bool(hit[3])) in {(s[0], s[1], s[3]) for s in shapes}:
             try:
                 h.set_launch(*hit[:3], streaming=bool(hit[3]))
                 return tuple(hit)
             except hap.HapError:
                 pass
     best, best_us = None, float("inf")
-    for shape in sweep_candidates(h.n, esz):
+    for shape in shapes:
         try:
             h.set_launch(*shape[:3], streaming=shape[3])
         except hap.HapError:

@@ -215,7 +215,6 @@ Launch default_launch(int64_t n, size_t esz) {
             lc.threads = 0;
             return lc;
         }
-        lc.held = esz == 4 && n <= 512 * 8 * 4;
     }
     // About 256 workgroups (one per CU) on large problems.  Small problems (FP32 up to 512
     // points, FP64 up to 2048) take one row per workgroup and sum the column partials in
@@ -1070,7 +1069,6 @@ hap_status hap_set_launch(hap_ctx *c, int32_t threads, int32_t chunks, int32_t r
     if (threads) lc.threads = threads;
     if (chunks) lc.chunks = chunks;
     if (rows_per_block) lc.rows_per_block = rows_per_block;
-    if (threads || chunks || flags >= 0) lc.held = false;   // the shape asked for
     if (flags >= 0) lc.streaming = (flags & HAP_LAUNCH_STREAM) != 0;
     if (flags >= 0) lc.blocks = (flags & HAP_LAUNCH_BLOCKS) != 0;
     lc.ordered = (lc.rows_per_block == 1);
@@ -1167,7 +1165,7 @@ hap_status hap_get_launch(hap_ctx *c, int32_t *threads, int32_t *chunks, int32_t
     if (flags)
         *flags = (c->lc.streaming ? HAP_LAUNCH_STREAM : 0) | (c->use_graphs ? 0 : HAP_LAUNCH_EAGER) |
                  (c->no_fuse ? HAP_LAUNCH_UNFUSED : 0) | (use_fused(c, c->lc) ? HAP_LAUNCH_FUSED : 0) |
-                 (c->lc.blocks ? HAP_LAUNCH_BLOCKS : 0);
+                 (c->lc.blocks ? HAP_LAUNCH_BLOCKS : 0) | (hap::runs_held(c->lc, c->n, c->esz) ? HAP_LAUNCH_HELD : 0);
     if (threads) *threads = c->lc.threads;
     if (chunks) *chunks = c->lc.chunks;
     if (rows_per_block) *rows_per_block = c->lc.rows_per_block;

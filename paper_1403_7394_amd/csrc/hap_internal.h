@@ -47,12 +47,18 @@ struct Launch {
     bool ordered;       // column partials summed strictly in workgroup order
     bool streaming;     // large rows: 1024 threads, phase 2 re-reads S and R (chunks 2..16); or, FP32
                         // with 512 threads x 16 chunks, the held-row pass (phase 2 reads nothing)
-    bool held = false;  // the default for FP32 rows of 8192 < n <= 16384: reported as the streaming shape,
-                        // run by the held-row pass (the same bits)
     bool blocks = false; // workgroup g takes rows [g rb, (g + 1) rb) instead of g, g + G, g + 2G, ...
                          // (G workgroups), the default, under which the rows in flight at any
                          // moment are neighbours in memory
 };
+// The held-row pass runs a streaming shape: its own (512 threads x 16 chunks), and in FP32 that of rows of
+// 8192 < n <= 16384 with the fewest chunks (1024 threads), the default there, to which it gives the same
+// bits faster.  A property of the shape alone, so a shape that is read back and set again runs the same pass.
+inline bool runs_held(const Launch &lc, int64_t n, size_t elem) {
+    if (!lc.streaming || elem != 4) return false;
+    if (lc.threads == 512) return lc.chunks == 16;
+    return lc.threads == 1024 && n > 512 * 4 * 4 && n <= 512 * 8 * 4 && lc.chunks == (int)((n + 4095) / 4096);
+}
 // Row stride of the row passes for this launch over `rows` rows (0: contiguous blocks).
 inline int row_stride_of(const Launch &lc, int rows) {
     if (lc.blocks || lc.rows_per_block <= 1) return 0;

@@ -1230,7 +1230,7 @@ hipError_t launch_sweep_level(const T *S, int64_t lds, const LevelPtrs<T> &lv, T
         }
         return hipErrorInvalidValue;
     }
-    if (lc.streaming && (lc.threads == 512 || lc.held)) {
+    if (lc.streaming && (lc.threads == 512 || runs_held(lc, n, sizeof(T)))) {
         // the held-row pass: FP32, 512 threads x 16 chunks (n <= 32768), of which rows of up to 16384
         // columns need only eight (and, of up to 12288, six): with the column sums, 10609 points
         // take 443 us a level (5.1 TB/s), 495 us streamed; 16384 points 988 and 1087

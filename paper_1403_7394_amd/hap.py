@@ -22,6 +22,7 @@ LAUNCH_STREAM = 2
 LAUNCH_EAGER = 4
 LAUNCH_UNFUSED = 8
 LAUNCH_FUSED = 16   # reported by hap_get_launch: the MapReduce levels run in one fused pass
+LAUNCH_HELD = 64    # reported by hap_get_launch: the held-row pass runs
 LAUNCH_BLOCKS = 32  # each workgroup takes a contiguous block of rows (default: rows interleaved)
 PROBE_CACHED, PROBE_BLOCKS = 1, 2
 SCHEDULE_SEQUENTIAL, SCHEDULE_MRHAP = 0, 1
