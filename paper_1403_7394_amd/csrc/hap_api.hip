@@ -272,6 +272,16 @@ bool partials_in_workspace(const hap_ctx *c, const Launch &lc, int64_t rows) {
 }
 
 
+// p points into memory of the context's device.
+bool on_device(const hap_ctx *c, const void *p) {
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == c->device;
+}
+
 bool dtype_ok(int32_t dt) { return dt == HAP_F32 || dt == HAP_F64; }
 size_t dtype_size(int32_t dt) { return dt == HAP_F64 ? 8 : 4; }
 
@@ -919,10 +929,14 @@ hap_status hap_exemplars(hap_ctx *c, int32_t level, int32_t *labels, int32_t *n_
         c->labels_ready = true;
     }
     const int32_t *src = c->Efinal + (size_t)c->ldw * level;
-    if (labels && !n_exemplars)
+    // the counting kernel writes the copy too, where it can: other memory goes through the runtime, which
+    // checks it
+    const bool counted = labels && n_exemplars && on_device(c, labels);
+    if (labels && !counted)
         HIP_TRY(hipMemcpyAsync(labels, src, (size_t)c->n * 4, hipMemcpyDeviceToDevice, c->stream), c);
     if (n_exemplars) {
-        HIP_TRY(hap::launch_count_distinct(src, (int)c->rows, (int)c->n, labels, c->count, c->stream), c);
+        HIP_TRY(hap::launch_count_distinct(src, (int)c->rows, (int)c->n, counted ? labels : nullptr, c->count, c->stream),
+                c);
         HIP_TRY(hipMemcpyAsync(n_exemplars, c->count, 4, hipMemcpyDeviceToHost, c->stream), c);
         HIP_TRY(hipStreamSynchronize(c->stream), c);
     }
