@@ -768,6 +768,19 @@ GemmArgs make_gemm(const float *A, int64_t sam, int64_t sak, const float *B, int
         if (_e != hipSuccess) return _e;     \
     } while (0)
 
+bool overlap(const float *a, int64_t na, const float *b, int64_t nb) {
+    const uintptr_t pa = (uintptr_t)a, pb = (uintptr_t)b;
+    return pa < pb + (uintptr_t)nb * 4 && pb < pa + (uintptr_t)na * 4;
+}
+
+// Rows of Y that touch no row of X but their own: columns of one matrix, either apart or of the same row.
+bool own_rows(const float *X, int64_t ldx, int n_in, const float *Y, int64_t ldy, int n_out) {
+    const int64_t bytes = (intptr_t)Y - (intptr_t)X, off = bytes / 4;
+    if (ldx != ldy || bytes % 4 != 0) return false;
+    const int64_t col = (off % ldx + ldx) % ldx;
+    return col + n_out <= ldx && (col >= n_in || off == col);
+}
+
 // Networks small enough for the fused kernels (register and LDS budgets set the limits).
 bool fuse_ok(int n_in, int hidden, int n_out) {
     return n_in <= kFuseIn && hidden <= kFuseHidden && n_out <= kFuseOut;
@@ -926,7 +939,13 @@ hipError_t layered_forward(const MlpLayout &lo, int n_in, int hidden, int n_out,
 hipError_t mlp_forward(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, const float *P,
                        const float *X, int64_t ldx, int rows, float *Y, int64_t ldy, char *ws, hipStream_t st) {
     if (rows <= 0) return hipSuccess;
-    if (!fuse_ok(n_in, hidden, n_out))
+    // The fused kernel writes outputs while other rows are still to be read; layer by layer, X has been read
+    // before Y is written, so that they may share memory (and the parameters of the first two layers).
+    const int64_t y_len = (int64_t)(rows - 1) * ldy + n_out;
+    const bool shared = (overlap(Y, y_len, X, (int64_t)(rows - 1) * ldx + n_in) &&
+                         !own_rows(X, ldx, n_in, Y, ldy, n_out)) ||
+                        overlap(Y, y_len, P, lo.count);
+    if (!fuse_ok(n_in, hidden, n_out) || shared)
         return layered_forward(lo, n_in, hidden, n_out, bf16, P, X, ldx, rows, Y, ldy, ws, st);
     FuseArgs g = fuse_args(lo, n_in, hidden, n_out, P, X, ldx, rows);
     g.Y = Y;
