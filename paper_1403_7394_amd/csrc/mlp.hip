@@ -276,8 +276,10 @@ constexpr int kFuseIn = 32, kFuseOut = 16, kFuseHidden = 256;
 constexpr int kFrag = 16 * kTile;   // elements of one block of 16 units over one tile
 
 // Where the training kernels keep a batch's operands in the workspace (bytes).  Fragments:
-// [block of 16 units][tile][kFrag] of X, H1, H2, dY, dH1, dH2; the unrounded dH1, dH2 and dY for the
-// bias gradients: [unit][row]; one squared-error sum per tile.
+// [block of 16 units][tile][kFrag] of X, H1, H2, dY, dH1, dH2; in BF16 the unrounded dH1, dH2 and dY for the
+// bias gradients too: [unit][row] (FP32 fragments hold them unrounded, a block as [row][16 units]; with a second
+// copy a batch of 65536 rows over 128 units took 215 MB instead of the 148 here, layer by layer 146); one
+// squared-error sum per tile.
 struct FuseLayout {
     int tiles, bh;         // tiles of rows; blocks of hidden units
     int64_t rows;          // tiles * kTile
@@ -310,9 +312,11 @@ FuseLayout fuse_layout(int hidden, int n_out, int64_t rows, bool bf16) {
     f.dY = take(frag);
     f.d1 = take(frag * f.bh);
     f.d2 = take(frag * f.bh);
-    f.f1 = take((size_t)f.rows * hidden * 4);
-    f.f2 = take((size_t)f.rows * hidden * 4);
-    f.fy = take((size_t)f.rows * n_out * 4);
+    if (bf16) {
+        f.f1 = take((size_t)f.rows * hidden * 4);
+        f.f2 = take((size_t)f.rows * hidden * 4);
+        f.fy = take((size_t)f.rows * n_out * 4);
+    }
     f.loss = take((size_t)f.tiles * 8);
     f.bytes = off;
     const int hp = padded_hidden(hidden);
@@ -541,7 +545,7 @@ __global__ __launch_bounds__(2 * HP) void mlp_tile_kernel(FuseArgs g) {
             }
             if constexpr (TRAIN) {
                 M::put(frag(g.fl.dY, 0), wid, kg, r16, dy);
-                if (r16 < n_out)
+                if (BF16 && r16 < n_out)
                     *(f32x4 *)((float *)(g.ws + g.fl.fy) + r16 * g.fl.rows + row0 + 16 * wid + 4 * kg) = dy;
 #pragma unroll
                 for (int off = 32; off >= 1; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
@@ -564,7 +568,7 @@ __global__ __launch_bounds__(2 * HP) void mlp_tile_kernel(FuseArgs g) {
                             if (keep) H2s[16 * rb + 4 * kg + r][col[c]] = M::cvt(v[r]);
                         }
                         if (wid * 2 + c < g.fl.bh) M::put(frag(region, wid * 2 + c), rb, kg, r16, v);
-                        if (col[c] < H)
+                        if (BF16 && col[c] < H)
                             *(f32x4 *)((float *)(g.ws + plain) + col[c] * g.fl.rows + row0 + 16 * rb + 4 * kg) = v;
                     }
             };
@@ -616,7 +620,8 @@ struct GradArgs {
 
 // Parameter gradients from a batch's operands.  Workgroups, in order: one per 16 x 16 tile of
 // gW2, gW1, gW3 (one wave, one accumulator, rows ascending; the loads of 16 tiles of rows are in flight
-// together), one per bias (256 threads, colsum_rows_kernel's sum), one for the loss.
+// together), one per bias (256 threads, colsum_rows_kernel's sum; FP32: one per block of 16 of them, whose
+// rows of a fragment a thread reads whole), one for the loss.
 template <bool BF16, bool ADAM>
 __global__ __launch_bounds__(256) void mlp_grad_kernel(GradArgs g) {
     using M = Mx<BF16>;
@@ -689,7 +694,37 @@ __global__ __launch_bounds__(256) void mlp_grad_kernel(GradArgs g) {
         return;
     }
     b -= n2 + n1 + n3;
-    if (b < 2 * g.H + g.n_out) {
+    const int biases = BF16 ? 2 * g.H + g.n_out : 2 * bh + 1;   // workgroups
+    if constexpr (!BF16) {
+        if (b < biases) {
+            // bias gradients: the sums of the columns of a block of dH1, dH2 or dY
+            __shared__ float part[4][16];
+            const size_t region = b < bh ? g.fl.d1 : b < 2 * bh ? g.fl.d2 : g.fl.dY;
+            const int blk = b < bh ? b : b < 2 * bh ? b - bh : 0;
+            const f32x4 *x = (const f32x4 *)((const float *)(g.ws + region) + (int64_t)blk * g.fl.rows * 16);
+            float acc[16] = {};
+#pragma unroll 4
+            for (int r = tid; r < g.rows; r += 256)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 v = x[(int64_t)r * 4 + q];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[4 * q + e] += v[e];
+                }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) acc[u] += __shfl_xor(acc[u], off, 64);
+                if (lane == 0) part[wid][u] = acc[u];
+            }
+            __syncthreads();
+            const int u = blk * 16 + tid;
+            if (tid < 16 && u < (b < 2 * bh ? g.H : g.n_out))
+                emit((b < bh ? g.lo.ob1 : b < 2 * bh ? g.lo.ob2 : g.lo.ob3) + u,
+                     (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]));
+            return;
+        }
+    } else if (b < biases) {
         // bias gradient: the sum of one unit's row of f1, f2 or fy
         __shared__ float part[4];
         const size_t region = b < g.H ? g.fl.f1 : b < 2 * g.H ? g.fl.f2 : g.fl.fy;
@@ -874,7 +909,7 @@ hipError_t run_train(const MlpLayout &lo, int n_in, int hidden, int n_out, bool 
     a.pack = packed ? ws : nullptr;
     a.hp = hp;
     const int bh = g.fl.bh;
-    const int grid = bh * bh + (n_in + 15) / 16 * bh + bh + 2 * hidden + n_out + 1;
+    const int grid = bh * bh + (n_in + 15) / 16 * bh + bh + (bf16 ? 2 * hidden + n_out : 2 * bh + 1) + 1;
     if (bf16)
         hipLaunchKernelGGL((mlp_grad_kernel<true, ADAM>), dim3(grid), dim3(256), 0, st, a);
     else
