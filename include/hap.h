@@ -347,8 +347,9 @@ HAP_API hap_status hap_get_row_count(hap_ctx *ctx, int64_t *rows);
  * context's stream around the launches.  enable = k >= 1 starts collecting (and
  * clears the totals) for the launches of every k-th sweep (1: every launch), 0 stops.
  * hap_profile_read returns the summed elapsed time (ms) and the count of the timed
- * launches of the row pass (Eq. 2.1-2.6 fused, one launch per level and iteration)
- * and of the column-sum epilogue (Eq. 2.4).  Timed sweeps are launched one kernel at
+ * launches of the row pass (Eq. 2.1-2.6 fused, one launch per level and iteration, or one per
+ * iteration of the all-level pass) and of the column-sum epilogue (Eq. 2.4), counted by level: the
+ * all-level pass's one launch per iteration counts once for each.  Timed sweeps are launched one kernel at
  * a time (never from a captured graph).  For the benchmark's roofline figure.
  */
 HAP_API hap_status hap_profile(hap_ctx *ctx, int32_t enable);

@@ -72,7 +72,7 @@ struct hap_ctx {
     long long prof_sweep = 0;     // sweeps issued since timing was switched on
     bool prof_now = false;        // the current sweep's launches are timed
     std::vector<hipEvent_t> ev;      // pairs: [2k] before, [2k+1] after launch k of the current chunk
-    std::vector<int> ev_kind;        // 0 = row pass, 1 = column sums
+    std::vector<int> ev_kind;        // 0 = row pass, 1 = column sums of a level, 2 = of every level
     int ev_used = 0;
     double prof_ms[2] = {0.0, 0.0};
     long long prof_n[2] = {0, 0};
@@ -316,8 +316,9 @@ hipError_t prof_collect(hap_ctx *c) {
         float ms = 0.f;
         hipError_t err = hipEventElapsedTime(&ms, c->ev[2 * k], c->ev[2 * k + 1]);
         if (err != hipSuccess) return err;
-        c->prof_ms[c->ev_kind[k]] += ms;
-        c->prof_n[c->ev_kind[k]] += 1;
+        const int kind = c->ev_kind[k];
+        c->prof_ms[kind > 0] += ms;
+        c->prof_n[kind > 0] += kind == 2 ? c->L : 1;
     }
     c->ev_used = 0;
     return hipSuccess;
@@ -385,7 +386,7 @@ hap_status run_sweeps(hap_ctx *c, int count, int K) {
         c->prof_now = c->prof && (c->prof_sweep++ % c->prof_period == 0);
         if (fused) {
             if constexpr (sizeof(T) == 4) {
-                // every level's row pass in one launch, then the column sums in level order
+                // every level's row pass in one launch, then every level's column sums in another
                 hap::FusedArgs<float> fa{};
                 fa.S = (const float *)c->S;
                 fa.lds = c->lds;
@@ -415,15 +416,9 @@ hap_status run_sweeps(hap_ctx *c, int count, int K) {
                 HIP_TRY(prof_mark(c, 0, false), c);
                 HIP_TRY(hap::launch_sweep_fused(fa, c->lc, c->stream), c);
                 HIP_TRY(prof_mark(c, 0, true), c);
-                if (c->prof) {
-                    // one launch per level, which hap_profile counts
-                    for (int l = 0; l < L; ++l) {
-                        const hap_status s = col(l, (T *)fa.Qpart[l], false);
-                        if (s != HAP_OK) return s;
-                    }
-                } else {
-                    HIP_TRY(hap::launch_colsum_levels(fa, fl, nb, K, c->lc.ordered, c->stream), c);
-                }
+                HIP_TRY(prof_mark(c, 2, false), c);
+                HIP_TRY(hap::launch_colsum_levels(fa, fl, nb, K, c->lc.ordered, c->stream), c);
+                HIP_TRY(prof_mark(c, 2, true), c);
                 continue;
             }
         }

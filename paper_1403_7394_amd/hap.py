@@ -403,7 +403,7 @@ class Hap:
         _check("hap_profile", self._lib.hap_profile(self._ctx, int(every) if enable else 0))
 
     def profile_read(self):
-        """(row pass ms, row pass launches, column-sum ms, column-sum launches)."""
+        """(row pass ms, row pass launches, column-sum ms, levels summed)."""
         a, b, c, d = ctypes.c_double(), ctypes.c_int64(), ctypes.c_double(), ctypes.c_int64()
         _check("hap_profile_read", self._lib.hap_profile_read(self._ctx, ctypes.byref(a), ctypes.byref(b),
                                                               ctypes.byref(c), ctypes.byref(d)))
