@@ -532,10 +532,16 @@ hipError_t launch_flow(const SweepArgs<T> &a, int threads, int nb, bool tail, hi
         return hipGetLastError();                                                                        \
     } while (0)
     // 1024 threads (128 registers each), as many rows in flight as fit them; rows of one wave: four, the
-    // most a workgroup has at these lengths by default
+    // most a workgroup has at these lengths by default.  Workgroups with fewer rows take fewer groups: idle
+    // ones hold waves back (2000 points with two rows 32.4 us a level with eight groups, 26.9 with two, 29.2
+    // one row at a time; in points mode 37.8, 30.4 and 33.8).
     if constexpr (D <= 0) {
         if (threads == 64 && a.rb <= 4) HAP_LAUNCH_FLOW(sweep_flow_one_kernel, 64, 4);
+        if (threads == 128 && a.rb <= 2) HAP_LAUNCH_FLOW(sweep_flow_one_kernel, 128, 2);
+        if (threads == 128 && a.rb <= 4) HAP_LAUNCH_FLOW(sweep_flow_one_kernel, 128, 4);
         if (threads == 128 && a.rb <= 8) HAP_LAUNCH_FLOW(sweep_flow_one_kernel, 128, 8);
+    } else {
+        if (threads == 128 && a.rb <= 2) HAP_LAUNCH_FLOW(sweep_flow_kernel, 128, 2);
     }
     if (threads == 64) HAP_LAUNCH_FLOW(sweep_flow_kernel, 64, 4);
     if (threads == 128) HAP_LAUNCH_FLOW(sweep_flow_kernel, 128, 8);
