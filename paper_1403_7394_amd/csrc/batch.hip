@@ -214,6 +214,7 @@ __device__ __forceinline__ void batch_rows(const SweepArgs<float> &a, const int 
 #pragma clang fp contract(off)
     using V = Vec<float>::type;
     constexpr int VW = 4, NWG = NTG / 64, CB = NTG * 16;
+    constexpr int AUX = NTG == 256 ? 0 : kNT;   // stores
     const int grp = G > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NTG) : 0;
     const int ltid = threadIdx.x % NTG, lane = ltid & 63, wid = __builtin_amdgcn_readfirstlane(ltid >> 6);
     const int n = a.n;
@@ -239,7 +240,7 @@ __device__ __forceinline__ void batch_rows(const SweepArgs<float> &a, const int 
         }
         float m1, m2, cv;
         int ck;
-        flow_phase1<float, NTG, NCH, FIRST, true, false>(
+        flow_phase1<float, NTG, NCH, FIRST, true, false, AUX>(
             x, i, n, wid, base, a.lam, a.oml, p, 0.f, rA, voff, m1, m2, cv, ck, [&](int, V &) {},
             [&](int c) { return Bv[c]; });
         ck = (ck == INT_MAX) ? INT_MAX : ck + base;
@@ -276,7 +277,7 @@ __device__ __forceinline__ void batch_rows(const SweepArgs<float> &a, const int 
                 chg |= (t >= 3 && e_old != ck) ? 1 : 0;
             }
         }
-        flow_phase2<float, NTG, NCH, true>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fminf(tau_i, -m1) : -m1,
+        flow_phase2<float, NTG, NCH, true, AUX>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fminf(tau_i, -m1) : -m1,
                                            has_tau ? fminf(tau_i, -m2) : -m2, rR, voff);
         if constexpr (G > 1) lds_wait(&L.turn[wid], i - row0);
 #pragma unroll

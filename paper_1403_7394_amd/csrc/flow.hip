@@ -3,7 +3,7 @@
 
 namespace hap {
 
-template hipError_t launch_flow<float, 0>(const SweepArgs<float> &, int, int, bool, hipStream_t);
-template hipError_t launch_flow<float, -1>(const SweepArgs<float> &, int, int, bool, hipStream_t);
+template hipError_t launch_flow<float, 0>(const SweepArgs<float> &, int, int, bool, bool, hipStream_t);
+template hipError_t launch_flow<float, -1>(const SweepArgs<float> &, int, int, bool, bool, hipStream_t);
 
 }  // namespace hap

@@ -22,7 +22,7 @@ struct FusedLds {
     int e[kMaxFused][kWin];
 };
 
-template <int NTG, int NCH, int RG, bool FIRST, bool TAIL>
+template <int NTG, int NCH, int RG, bool FIRST, bool TAIL, int AUX>
 __device__ __forceinline__ void fused_flow_rows(const FusedArgs<float> &a, const int t, const int row0, const int row1,
                                                 FusedLds<NTG, NCH, RG> &L) {
 #pragma clang fp contract(off)
@@ -31,7 +31,6 @@ __device__ __forceinline__ void fused_flow_rows(const FusedArgs<float> &a, const
     constexpr int VW = 4;
     constexpr int NWG = NTG / 64;
     constexpr int CB = NTG * 16;
-    constexpr int AUX = flow_policy<NTG>();
     const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x / NTG);
     const int ltid = threadIdx.x % NTG, lane = ltid & 63, wid = __builtin_amdgcn_readfirstlane(ltid >> 6);
     const int n = a.n;
@@ -58,7 +57,7 @@ __device__ __forceinline__ void fused_flow_rows(const FusedArgs<float> &a, const
             }
             T m1, m2, cv;
             int ck;
-            flow_phase1<T, NTG, NCH, FIRST, TAIL, false>(
+            flow_phase1<T, NTG, NCH, FIRST, TAIL, false, AUX>(
                 x, i, n, wid, base, a.lam, a.oml, L.p[l][r], 0.f, rA, voff, m1, m2, cv, ck,
                 [&](int c, V &s) { s = sx[c]; }, [&](int c) { return L.b[l][c][ltid]; });
             ck = (ck == INT_MAX) ? INT_MAX : ck + base;
@@ -105,7 +104,7 @@ __device__ __forceinline__ void fused_flow_rows(const FusedArgs<float> &a, const
                 }
             }
             c_below = cv;
-            flow_phase2<T, NTG, NCH, TAIL>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fmin(tau_i, -m1) : -m1,
+            flow_phase2<T, NTG, NCH, TAIL, AUX>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fmin(tau_i, -m1) : -m1,
                                            has_tau ? fmin(tau_i, -m2) : -m2, rR, voff);
             lds_wait(&L.turn[l][wid], r);
 #pragma unroll
@@ -124,7 +123,7 @@ __device__ __forceinline__ void fused_flow_rows(const FusedArgs<float> &a, const
     if (chg) atomicOr(&a.ds->changed, 1);
 }
 
-template <int NTG, int RG, bool TAIL>
+template <int NTG, int RG, bool TAIL, int AUX = kNT>
 __global__ __launch_bounds__(NTG *RG) void sweep_fused_flow_kernel(FusedArgs<float> a) {
 #pragma clang fp contract(off)
     using V = Vec<float>::type;
@@ -153,9 +152,9 @@ __global__ __launch_bounds__(NTG *RG) void sweep_fused_flow_kernel(FusedArgs<flo
     if (tid < RG) L.arrived[tid] = 0;
     __syncthreads();
     if (t == 1)
-        fused_flow_rows<NTG, NCH, RG, true, TAIL>(a, t, row0, row1, L);
+        fused_flow_rows<NTG, NCH, RG, true, TAIL, AUX>(a, t, row0, row1, L);
     else
-        fused_flow_rows<NTG, NCH, RG, false, TAIL>(a, t, row0, row1, L);
+        fused_flow_rows<NTG, NCH, RG, false, TAIL, AUX>(a, t, row0, row1, L);
     __syncthreads();
     for (int l = 0; l < a.L; ++l) {
         float *qrow = a.Qpart[l] + (int64_t)blockIdx.x * a.ldw;
@@ -169,12 +168,14 @@ __global__ __launch_bounds__(NTG *RG) void sweep_fused_flow_kernel(FusedArgs<flo
 }  // namespace
 
 hipError_t launch_fused_flow(const FusedArgs<float> &a, int threads, int nb, bool tail, hipStream_t st) {
-#define HAP_LAUNCH(NTG, RG)                                                                                     \
+#define HAP_LAUNCH(NTG, RG, ...)                                                                                \
     do {                                                                                                        \
         if (tail)                                                                                               \
-            hipLaunchKernelGGL((sweep_fused_flow_kernel<NTG, RG, true>), dim3(nb), dim3(NTG * RG), 0, st, a);   \
+            hipLaunchKernelGGL((sweep_fused_flow_kernel<NTG, RG, true __VA_OPT__(, ) __VA_ARGS__>), dim3(nb),   \
+                               dim3(NTG * RG), 0, st, a);                                                       \
         else                                                                                                    \
-            hipLaunchKernelGGL((sweep_fused_flow_kernel<NTG, RG, false>), dim3(nb), dim3(NTG * RG), 0, st, a);  \
+            hipLaunchKernelGGL((sweep_fused_flow_kernel<NTG, RG, false __VA_OPT__(, ) __VA_ARGS__>), dim3(nb),  \
+                               dim3(NTG * RG), 0, st, a);                                                       \
         return hipGetLastError();                                                                               \
     } while (0)
     if (threads == 64) HAP_LAUNCH(64, 4);
@@ -183,6 +184,7 @@ hipError_t launch_fused_flow(const FusedArgs<float> &a, int threads, int nb, boo
     if (threads == 128 && a.rb <= 2) HAP_LAUNCH(128, 2);
     if (threads == 128 && a.rb <= 4) HAP_LAUNCH(128, 4);
     if (threads == 128) HAP_LAUNCH(128, 8);
+    if (threads == 256 && a.cached) HAP_LAUNCH(256, 4, 0);
     if (threads == 256) HAP_LAUNCH(256, 4);
 #undef HAP_LAUNCH
     return hipErrorInvalidValue;

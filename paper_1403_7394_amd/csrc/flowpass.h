@@ -22,12 +22,17 @@
 
 namespace hap {
 
-// Cache policy of a row's loads and stores.  Every word is touched once a pass, so non-temporal,
-// except rows of 256 threads (FP32 up to 4096 columns): there a level's matrices stay in the 256 MB
-// Infinity Cache from pass to pass (3000 points 40.1 -> 36.4 us a level with column sums, 4096 points
-// 65.8 -> 63.5), while longer rows lose (6000 points 136 -> 152 us) and so do shorter ones (2000
-// points 20.6 -> 22.2 us).
-template <int NTG> constexpr int flow_policy() { return NTG == 256 ? 0 : kNT; }
+// Cache policy (AUX) of a row's loads and stores.  Every word is touched once a pass, so non-temporal, except
+// rows of 256 threads (FP32 up to 4096 columns): there matrices stay in the 256 MB Infinity Cache from pass to
+// pass, and the accesses are cached where they pay (us a level, non-temporal and cached):
+//   - S and the messages of every level fit it together: 3000 points, two levels, 12 rows 41.2, 37.6, three
+//     rows 50.7, 48.2;
+//   - or they do not, and a workgroup has more than four rows: 4000 points, two levels (320 MB), 16 rows 66.6,
+//     62.9, but three rows 77.7, 83.3;
+//   - the all-level pass goes through every level's matrices at once, so their sum decides: 3800 points, two
+//     levels (289 MB) 53.1, 48.9, 4096 (336 MB) 59.9, 58.2, but three levels of 3500 (343 MB) 44.2, 45.0 and of
+//     4000 (448 MB) 56.7, 61.3.
+// Longer rows lose (6000 points 136 -> 152 us) and so do shorter ones (2000 points 20.6 -> 22.2 us).
 
 template <typename T, int NTG, int NCH, int RG, int D>
 struct FlowLds {
@@ -117,7 +122,7 @@ struct FlowRow {
 
 // Phase 1 of row i: finish alpha^{t-1} (stored through rA), reduce (M1, M2) of alpha + s and
 // (c, e) of alpha + rho over this thread's columns.  make_s(c): s of chunk c in points mode.
-template <typename T, int NTG, int NCH, bool FIRST, bool TAIL, bool OFFSET, typename MakeS, typename BaseOf>
+template <typename T, int NTG, int NCH, bool FIRST, bool TAIL, bool OFFSET, int AUX, typename MakeS, typename BaseOf>
 __device__ __forceinline__ void flow_phase1(FlowRow<T, NTG, NCH> &x, int i, int n, int wid, int base, T lam, T oml,
                                             T p_i, T d_i, const __amdgpu_buffer_rsrc_t rA, int voff, T &m1, T &m2,
                                             T &cv, int &ck, MakeS make_s, BaseOf base_of) {
@@ -175,14 +180,14 @@ __device__ __forceinline__ void flow_phase1(FlowRow<T, NTG, NCH> &x, int i, int 
             m2 = second_max(m1, m2, y[v]);
             m1 = y[v] > m1 ? y[v] : m1;
         }
-        if constexpr (!FIRST) buf_store<V, flow_policy<NTG>()>(x.a[c], rA, voff, c * CB);
+        if constexpr (!FIRST) buf_store<V, AUX>(x.a[c], rA, voff, c * CB);
         x.a[c] = y;
     }
 }
 
 // Phase 2 of row i: rho^t (stored through rR); s becomes the row's contribution to the column sums.
 // u1, u2: min(tau_i, -M1) and min(tau_i, -M2).
-template <typename T, int NTG, int NCH, bool TAIL>
+template <typename T, int NTG, int NCH, bool TAIL, int AUX>
 __device__ __forceinline__ void flow_phase2(FlowRow<T, NTG, NCH> &x, int i, int n, int wid, int base, T lam, T oml, T m1,
                                             T u1, T u2, const __amdgpu_buffer_rsrc_t rR, int voff) {
 #pragma clang fp contract(off)
@@ -208,11 +213,11 @@ __device__ __forceinline__ void flow_phase2(FlowRow<T, NTG, NCH> &x, int i, int 
             for (int v = 0; v < VW; ++v)
                 if (c * NTG * VW + base + v == i) x.s[c][v] = out[v];
         }
-        buf_store<V, flow_policy<NTG>()>(out, rR, voff, c * CB);
+        buf_store<V, AUX>(out, rR, voff, c * CB);
     }
 }
 
-template <typename T, int NTG, int NCH, int RG, bool FIRST, bool TAIL, int D>
+template <typename T, int NTG, int NCH, int RG, bool FIRST, bool TAIL, int D, int AUX>
 __device__ __forceinline__ void flow_rows(const SweepArgs<T> &a, const int t, const int row0, const int row1,
                                           const typename Vec<T>::type (&Bv)[NCH],
                                           FlowLds<T, NTG, NCH, RG, D> &L) {
@@ -240,14 +245,14 @@ __device__ __forceinline__ void flow_rows(const SweepArgs<T> &a, const int t, co
             const __amdgpu_buffer_rsrc_t rS = row_rsrc(a.S + (int64_t)i * a.lds, row_bytes);
 #pragma unroll
             for (int c = 0; c < NCH; ++c) {
-                if constexpr (D <= 0) x.s[c] = buf_load<V, flow_policy<NTG>()>(rS, voff, c * CB);
-                x.r[c] = buf_load<V, flow_policy<NTG>()>(rR, voff, c * CB);
-                x.a[c] = buf_load<V, flow_policy<NTG>()>(rA, voff, c * CB);
+                if constexpr (D <= 0) x.s[c] = buf_load<V, AUX>(rS, voff, c * CB);
+                x.r[c] = buf_load<V, AUX>(rR, voff, c * CB);
+                x.a[c] = buf_load<V, AUX>(rA, voff, c * CB);
             }
         }
         T m1, m2, cv;
         int ck;
-        flow_phase1<T, NTG, NCH, FIRST, TAIL, (D < 0)>(
+        flow_phase1<T, NTG, NCH, FIRST, TAIL, (D < 0), AUX>(
             x, i, n, wid, base, a.lam, a.oml, L.p[r], L.d[r], rA, voff, m1, m2, cv, ck,
             [&](int c, V &s) {
                 if constexpr (D > 0) {
@@ -307,7 +312,7 @@ __device__ __forceinline__ void flow_rows(const SweepArgs<T> &a, const int t, co
             if (a.phi_down && (!FIRST || a.mrhap)) a.phi_down[i] = m1;
             if (a.tau_store) a.tau_store[i] = has_tau ? tau_i : pos_inf<T>();
         }
-        flow_phase2<T, NTG, NCH, TAIL>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fmin(tau_i, -m1) : -m1,
+        flow_phase2<T, NTG, NCH, TAIL, AUX>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fmin(tau_i, -m1) : -m1,
                                        has_tau ? fmin(tau_i, -m2) : -m2, rR, voff);
         if constexpr (RG > 1) lds_wait(&L.turn[wid], r);
 #pragma unroll
@@ -326,7 +331,7 @@ __device__ __forceinline__ void flow_rows(const SweepArgs<T> &a, const int t, co
     if (chg) atomicOr(&a.ds->changed, 1);
 }
 
-template <typename T, int NTG, int NCH, int RG, bool TAIL, int D>
+template <typename T, int NTG, int NCH, int RG, bool TAIL, int D, int AUX = kNT>
 __global__ __launch_bounds__(NTG *RG) void sweep_flow_kernel(SweepArgs<T> a) {
 #pragma clang fp contract(off)
     using V = typename Vec<T>::type;
@@ -369,9 +374,9 @@ __global__ __launch_bounds__(NTG *RG) void sweep_flow_kernel(SweepArgs<T> a) {
     }
     __syncthreads();
     if (t == 1)
-        flow_rows<T, NTG, NCH, RG, true, TAIL, D>(a, t, row0, row1, Bv, L);
+        flow_rows<T, NTG, NCH, RG, true, TAIL, D, AUX>(a, t, row0, row1, Bv, L);
     else
-        flow_rows<T, NTG, NCH, RG, false, TAIL, D>(a, t, row0, row1, Bv, L);
+        flow_rows<T, NTG, NCH, RG, false, TAIL, D, AUX>(a, t, row0, row1, Bv, L);
     __syncthreads();
     T *qrow = a.Qpart + (int64_t)blockIdx.x * a.ldw;
     for (int e = tid; e < NCH * NTG; e += NT) {
@@ -403,7 +408,7 @@ __device__ __forceinline__ void flow_one(const SweepArgs<T> &a, const int t, con
     const __amdgpu_buffer_rsrc_t rA = row_rsrc(a.A + (int64_t)i * a.ldw, row_bytes);
     T m1, m2, cv;
     int ck;
-    flow_phase1<T, NTG, NCH, FIRST, TAIL, (D < 0)>(
+    flow_phase1<T, NTG, NCH, FIRST, TAIL, (D < 0), kNT>(
         x, i, n, wid, base, a.lam, a.oml, p_i, d_i, rA, voff, m1, m2, cv, ck,
         [&](int, V &) {}, [&](int c) { return Bv[c]; });
     ck = (ck == INT_MAX) ? INT_MAX : ck + base;
@@ -426,7 +431,7 @@ __device__ __forceinline__ void flow_one(const SweepArgs<T> &a, const int t, con
         m1 = lane63(m1);
         m2 = lane63(m2);
     }
-    flow_phase2<T, NTG, NCH, TAIL>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fmin(tau_i, -m1) : -m1,
+    flow_phase2<T, NTG, NCH, TAIL, kNT>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fmin(tau_i, -m1) : -m1,
                                    has_tau ? fmin(tau_i, -m2) : -m2, rR, voff);
 #pragma unroll
     for (int c = 0; c < NCH; ++c) L.q[grp][c][ltid] = x.s[c];
@@ -476,9 +481,9 @@ __global__ __launch_bounds__(NTG *RG) void sweep_flow_one_kernel(SweepArgs<T> a)
         const __amdgpu_buffer_rsrc_t rB = row_rsrc(a.B, row_bytes);
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            x.s[c] = buf_load<V, flow_policy<NTG>()>(rS, ltid * 16, c * CB);
-            x.r[c] = buf_load<V, flow_policy<NTG>()>(rR, ltid * 16, c * CB);
-            x.a[c] = buf_load<V, flow_policy<NTG>()>(rA, ltid * 16, c * CB);
+            x.s[c] = buf_load<V, kNT>(rS, ltid * 16, c * CB);
+            x.r[c] = buf_load<V, kNT>(rR, ltid * 16, c * CB);
+            x.a[c] = buf_load<V, kNT>(rA, ltid * 16, c * CB);
             Bv[c] = buf_load<V, 0>(rB, ltid * 16, c * CB);
         }
         p_i = a.pref[i];
@@ -522,13 +527,13 @@ __global__ __launch_bounds__(NTG *RG) void sweep_flow_one_kernel(SweepArgs<T> a)
 }
 
 template <typename T, int D>
-hipError_t launch_flow(const SweepArgs<T> &a, int threads, int nb, bool tail, hipStream_t st) {
-#define HAP_LAUNCH_FLOW(KERNEL, NTG, RG)                                                                 \
+hipError_t launch_flow(const SweepArgs<T> &a, int threads, int nb, bool tail, bool fits, hipStream_t st) {
+#define HAP_LAUNCH_FLOW(KERNEL, NTG, RG, ...)                                                            \
     do {                                                                                                 \
         if (tail)                                                                                        \
-            hipLaunchKernelGGL((KERNEL<T, NTG, 4, RG, true, D>), dim3(nb), dim3(NTG * RG), 0, st, a);    \
+            hipLaunchKernelGGL((KERNEL<T, NTG, 4, RG, true, D __VA_OPT__(, ) __VA_ARGS__>), dim3(nb), dim3(NTG * RG), 0, st, a);  \
         else                                                                                             \
-            hipLaunchKernelGGL((KERNEL<T, NTG, 4, RG, false, D>), dim3(nb), dim3(NTG * RG), 0, st, a);   \
+            hipLaunchKernelGGL((KERNEL<T, NTG, 4, RG, false, D __VA_OPT__(, ) __VA_ARGS__>), dim3(nb), dim3(NTG * RG), 0, st, a); \
         return hipGetLastError();                                                                        \
     } while (0)
     // 1024 threads (128 registers each), as many rows in flight as fit them; rows of one wave: four, the
@@ -545,6 +550,7 @@ hipError_t launch_flow(const SweepArgs<T> &a, int threads, int nb, bool tail, hi
     }
     if (threads == 64) HAP_LAUNCH_FLOW(sweep_flow_kernel, 64, 4);
     if (threads == 128) HAP_LAUNCH_FLOW(sweep_flow_kernel, 128, 8);
+    if (threads == 256 && (fits || a.rb > 4)) HAP_LAUNCH_FLOW(sweep_flow_kernel, 256, 4, 0);
     if (threads == 256) HAP_LAUNCH_FLOW(sweep_flow_kernel, 256, 4);
     if (threads == 512) HAP_LAUNCH_FLOW(sweep_flow_kernel, 512, 2);
 #undef HAP_LAUNCH_FLOW

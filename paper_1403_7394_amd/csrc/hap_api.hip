@@ -340,7 +340,9 @@ hap_status run_sweeps(hap_ctx *c, int count, int K) {
     ex.ldx = c->ldx;
     ex.d = c->d;
     ex.rows = (int)c->rows;
-    ex.keep = c->kappa == 0.0 && (2 * (int64_t)L + 1) * c->rows * c->ldw * (int64_t)sizeof(T) <= ((int64_t)256 << 20);
+    const int64_t state = (2 * (int64_t)L + 1) * c->rows * c->ldw * (int64_t)sizeof(T);
+    ex.fits = state <= ((int64_t)256 << 20);
+    ex.keep = ex.fits && c->kappa == 0.0;
     const bool kappa = c->kappa != 0.0;
     auto row = [&](int l, T *qp) -> hap_status {
         LevelPtrs<T> lv = level_ptrs<T>(c, l);
@@ -396,6 +398,7 @@ hap_status run_sweeps(hap_ctx *c, int count, int K) {
                 fa.rb = c->lc.rows_per_block;
                 fa.row_stride = hap::row_stride_of(c->lc, c->rows);
                 fa.L = L;
+                fa.cached = state <= ((int64_t)320 << 20);
                 fa.lam = (float)c->lam;
                 fa.oml = (float)(1.0 - c->lam);
                 fa.ds = c->ds;

@@ -97,7 +97,8 @@ struct SweepExtra {
     uint64_t *pair_slots = nullptr;   // the paired row pass's exchange slots (kPairSlotWords per pair)
     uint64_t pair_wait = 0;           // wall-clock ticks one of its waits may take
     int pair_level = 0;               // the level this launch updates (part of the exchange tags)
-    bool keep = false;                // S and every level's rho and alpha fit the Infinity Cache together
+    bool fits = false;                // S and every level's rho and alpha fit the Infinity Cache together
+    bool keep = false;                // the same, without the Eq. 2.7 update's passes between the sweeps
 };
 // The paired row pass (FP32 rows of 32768 < n <= 65536, two workgroups per block of rows):
 // exchange slots in device memory, 20 words per pair, initialised to all ones (a tag no row
@@ -154,6 +155,7 @@ struct FusedArgs {
     int n, rows, rb, L;
     int row_stride;   // row order of a workgroup, as in the per-level row passes
     T lam, oml;
+    bool cached;      // cached accesses of rows of 256 threads (flowpass.h)
     DevState *ds;
     T *R[kMaxFused];
     T *A[kMaxFused];

@@ -10,6 +10,9 @@ namespace hap {
 
 namespace {
 
+// cached stores where a level's matrices stay in the Infinity Cache (rows of 256 threads), as in flowpass.h
+template <int NTG> constexpr int kRowAux = NTG == 256 ? 0 : kNT;
+
 template <typename T, int NTG, bool FIRST, bool TAIL, int D>
 __device__ __forceinline__ void one_row(const SweepArgs<T> &a, const int t, const int i,
                                         FlowRow<T, NTG, 4> &x, const typename Vec<T>::type (&Bv)[4], const T p_i,
@@ -27,7 +30,7 @@ __device__ __forceinline__ void one_row(const SweepArgs<T> &a, const int t, cons
     const __amdgpu_buffer_rsrc_t rA = row_rsrc(a.A + (int64_t)i * a.ldw, row_bytes);
     T m1, m2, cv;
     int ck;
-    flow_phase1<T, NTG, NCH, FIRST, TAIL, (D < 0)>(
+    flow_phase1<T, NTG, NCH, FIRST, TAIL, (D < 0), kRowAux<NTG>>(
         x, i, n, wid, base, a.lam, a.oml, p_i, d_i, rA, voff, m1, m2, cv, ck,
         [&](int c, V &s) {
             if constexpr (D > 0) {
@@ -66,7 +69,7 @@ __device__ __forceinline__ void one_row(const SweepArgs<T> &a, const int t, cons
         m1 = lane63(m1);
         m2 = lane63(m2);
     }
-    flow_phase2<T, NTG, NCH, TAIL>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fmin(tau_i, -m1) : -m1,
+    flow_phase2<T, NTG, NCH, TAIL, kRowAux<NTG>>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fmin(tau_i, -m1) : -m1,
                                    has_tau ? fmin(tau_i, -m2) : -m2, rR, voff);
     const __amdgpu_buffer_rsrc_t rQ = row_rsrc(a.Qpart + (int64_t)blockIdx.x * a.ldw, row_bytes);
 #pragma unroll

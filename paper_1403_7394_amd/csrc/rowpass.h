@@ -599,9 +599,10 @@ __device__ __forceinline__ void sweep_rows_points(const SweepArgs<T> &a, const i
 }
 
 // The row pass with several rows of a workgroup in flight (flowpass.h): threads per row 64, 128, 256 or
-// 512, four chunks per thread, nb workgroups of a.rb rows (2..kWin).
+// 512, four chunks per thread, nb workgroups of a.rb rows (2..kWin); fits as in
+// SweepExtra.
 template <typename T, int D>
-hipError_t launch_flow(const SweepArgs<T> &a, int threads, int nb, bool tail, hipStream_t st);
+hipError_t launch_flow(const SweepArgs<T> &a, int threads, int nb, bool tail, bool fits, hipStream_t st);
 
 // The row pass with one row per workgroup (row1.hip): threads per row 64 to 512, four chunks per thread.
 template <typename T, int D>

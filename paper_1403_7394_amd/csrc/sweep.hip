@@ -1265,10 +1265,10 @@ hipError_t launch_sweep_level(const T *S, int64_t lds, const LevelPtrs<T> &lv, T
     const bool reads_s = ex.delta != nullptr || X == nullptr;
     if constexpr (sizeof(T) == 4) {
         if (flow_fits(lc, sizeof(T), reads_s, tail)) {
-            if (ex.delta != nullptr) return launch_flow<T, -1>(a, lc.threads, nb, tail, st);
-            if (X == nullptr) return launch_flow<T, 0>(a, lc.threads, nb, tail, st);
-            if (d == 2) return launch_flow<T, 2>(a, lc.threads, nb, tail, st);
-            if (d == 3) return launch_flow<T, 3>(a, lc.threads, nb, tail, st);
+            if (ex.delta != nullptr) return launch_flow<T, -1>(a, lc.threads, nb, tail, ex.fits, st);
+            if (X == nullptr) return launch_flow<T, 0>(a, lc.threads, nb, tail, ex.fits, st);
+            if (d == 2) return launch_flow<T, 2>(a, lc.threads, nb, tail, ex.fits, st);
+            if (d == 3) return launch_flow<T, 3>(a, lc.threads, nb, tail, ex.fits, st);
         }
     }
     if (lc.rows_per_block == 1 && lc.chunks == 4 && lc.threads <= 512) {
