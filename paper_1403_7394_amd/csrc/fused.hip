@@ -275,7 +275,10 @@ hipError_t launch_sweep_fused(const FusedArgs<float> &a, const Launch &lc, hipSt
     } while (0)
     // several rows in flight wherever the bases and column sums of four levels fit the LDS (rows of up to
     // 4096 columns) and a workgroup's rows are staged at once
-    if (lc.threads < 512 && a.rb <= kWin) return launch_fused_flow(a, lc.threads, nb, tail, st);
+    // (two rows of 256 threads cannot hide their latency: 3500 points, two levels 61.3 us a level one row at a
+    // time and 65.4 with both in flight, 3000 points 55 and 48)
+    const bool two_long = lc.threads == 256 && a.rb == 2 && a.n > 3250;
+    if (lc.threads < 512 && a.rb <= kWin && !two_long) return launch_fused_flow(a, lc.threads, nb, tail, st);
     switch (lc.threads) {
         case 64: HAP_LAUNCH_FUSED(64); break;
         case 128: HAP_LAUNCH_FUSED(128); break;
