@@ -619,9 +619,9 @@ struct GradArgs {
 };
 
 // Parameter gradients from a batch's operands.  Workgroups, in order: one per 16 x 16 tile of
-// gW2, gW1, gW3 (one wave, one accumulator, rows ascending; the loads of 16 tiles of rows are in flight
-// together), one per bias (256 threads, colsum_rows_kernel's sum; FP32: one per block of 16 of them, whose
-// rows of a fragment a thread reads whole), one for the loss.
+// gW2, gW1, gW3 (one wave, one accumulator, rows ascending; the loads of 24 tiles of rows in BF16, of 4 in
+// FP32, are in flight together), one per bias (256 threads, colsum_rows_kernel's sum; FP32: one per four of them, a
+// quarter of a fragment's row per thread), one for the loss.
 template <bool BF16, bool ADAM>
 __global__ __launch_bounds__(256) void mlp_grad_kernel(GradArgs g) {
     using M = Mx<BF16>;
@@ -694,32 +694,27 @@ __global__ __launch_bounds__(256) void mlp_grad_kernel(GradArgs g) {
         return;
     }
     b -= n2 + n1 + n3;
-    const int biases = BF16 ? 2 * g.H + g.n_out : 2 * bh + 1;   // workgroups
+    const int biases = BF16 ? 2 * g.H + g.n_out : 4 * (2 * bh + 1);   // workgroups
     if constexpr (!BF16) {
         if (b < biases) {
-            // bias gradients: the sums of the columns of a block of dH1, dH2 or dY
-            __shared__ float part[4][16];
+            // bias gradients: the sums of four columns of a block of dH1, dH2 or dY
+            __shared__ f32x4 part[4];
+            const int four = b & 3;
+            b >>= 2;
             const size_t region = b < bh ? g.fl.d1 : b < 2 * bh ? g.fl.d2 : g.fl.dY;
             const int blk = b < bh ? b : b < 2 * bh ? b - bh : 0;
-            const f32x4 *x = (const f32x4 *)((const float *)(g.ws + region) + (int64_t)blk * g.fl.rows * 16);
-            float acc[16] = {};
-#pragma unroll 4
-            for (int r = tid; r < g.rows; r += 256)
+            const f32x4 *x = (const f32x4 *)((const float *)(g.ws + region) + (int64_t)blk * g.fl.rows * 16) + four;
+            f32x4 acc = (f32x4)(0.f);
+#pragma unroll 8
+            for (int r = tid; r < g.rows; r += 256) acc += x[(int64_t)r * 4];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const f32x4 v = x[(int64_t)r * 4 + q];
+            for (int off = 32; off >= 1; off >>= 1)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[4 * q + e] += v[e];
-                }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) acc[u] += __shfl_xor(acc[u], off, 64);
-                if (lane == 0) part[wid][u] = acc[u];
-            }
+                for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], off, 64);
+            if (lane == 0) part[wid] = acc;
             __syncthreads();
-            const int u = blk * 16 + tid;
-            if (tid < 16 && u < (b < 2 * bh ? g.H : g.n_out))
+            const int u = blk * 16 + four * 4 + tid;
+            if (tid < 4 && u < (b < 2 * bh ? g.H : g.n_out))
                 emit((b < bh ? g.lo.ob1 : b < 2 * bh ? g.lo.ob2 : g.lo.ob3) + u,
                      (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]));
             return;
@@ -909,7 +904,7 @@ hipError_t run_train(const MlpLayout &lo, int n_in, int hidden, int n_out, bool 
     a.pack = packed ? ws : nullptr;
     a.hp = hp;
     const int bh = g.fl.bh;
-    const int grid = bh * bh + (n_in + 15) / 16 * bh + bh + (bf16 ? 2 * hidden + n_out : 2 * bh + 1) + 1;
+    const int grid = bh * bh + (n_in + 15) / 16 * bh + bh + (bf16 ? 2 * hidden + n_out : 4 * (2 * bh + 1)) + 1;
     if (bf16)
         hipLaunchKernelGGL((mlp_grad_kernel<true, ADAM>), dim3(grid), dim3(256), 0, st, a);
     else
