@@ -196,6 +196,8 @@ __device__ float median_instance(const float *__restrict__ S, int n, int ld, uns
 // Measured at the default shape (512 threads, four groups) against groups that meet at a workgroup barrier
 // per step: 512 problems of 64..2048 points, 20 iterations, 280 -> 235 ms; 200 problems of 32..500
 // points, 40 iterations, 65 -> 22 ms; 256 of 32..200 points 17.0 -> 5.2 ms.
+// Loads and stores are non-temporal: the problems in flight are past every cache together (512 problems, 50
+// iterations with 1024 threads and four groups 566 ms with cached stores, 521 without).
 // Its LDS is indexed by column vector and by wave, so it is the same for every cut into groups.
 constexpr int kBatchVecs = 512;     // column vectors of the longest row (2048 points)
 template <int NT>
@@ -214,7 +216,6 @@ __device__ __forceinline__ void batch_rows(const SweepArgs<float> &a, const int 
 #pragma clang fp contract(off)
     using V = Vec<float>::type;
     constexpr int VW = 4, NWG = NTG / 64, CB = NTG * 16;
-    constexpr int AUX = NTG == 256 ? 0 : kNT;   // stores
     const int grp = G > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / NTG) : 0;
     const int ltid = threadIdx.x % NTG, lane = ltid & 63, wid = __builtin_amdgcn_readfirstlane(ltid >> 6);
     const int n = a.n;
@@ -240,7 +241,7 @@ __device__ __forceinline__ void batch_rows(const SweepArgs<float> &a, const int 
         }
         float m1, m2, cv;
         int ck;
-        flow_phase1<float, NTG, NCH, FIRST, true, false, AUX>(
+        flow_phase1<float, NTG, NCH, FIRST, true, false, kNT>(
             x, i, n, wid, base, a.lam, a.oml, p, 0.f, rA, voff, m1, m2, cv, ck, [&](int, V &) {},
             [&](int c) { return Bv[c]; });
         ck = (ck == INT_MAX) ? INT_MAX : ck + base;
@@ -277,7 +278,7 @@ __device__ __forceinline__ void batch_rows(const SweepArgs<float> &a, const int 
                 chg |= (t >= 3 && e_old != ck) ? 1 : 0;
             }
         }
-        flow_phase2<float, NTG, NCH, true, AUX>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fminf(tau_i, -m1) : -m1,
+        flow_phase2<float, NTG, NCH, true, kNT>(x, i, n, wid, base, a.lam, a.oml, m1, has_tau ? fminf(tau_i, -m1) : -m1,
                                            has_tau ? fminf(tau_i, -m2) : -m2, rR, voff);
         if constexpr (G > 1) lds_wait(&L.turn[wid], i - row0);
 #pragma unroll
