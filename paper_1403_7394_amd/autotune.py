@@ -86,7 +86,7 @@ def tune_sweep(h: "hap.Hap", sweeps: int = 3, use_cache: bool = True):
     """Pick the fastest row-pass shape for this problem and set it on h.  Runs sweeps on h,
     so call it on a context whose iteration state may be consumed (or re-create it)."""
     esz = 4 if str(h.dtype).endswith("float32") else 8
-    key = f"sweep:{_arch()}:n{_bucket(h.n)}:e{esz}"
+    key = f"sweep2:{_arch()}:n{_bucket(h.n)}:e{esz}"
     # the shape in effect (the library's choice, as a rule) is one of those timed
     shapes = [h.get_launch()]
     shapes += [s for s in sweep_candidates(h.n, esz) if s != shapes[0]]
@@ -152,7 +152,7 @@ def tune_batch(bt: "hap.HapBatch", X, damping: float, iters: int = 50, use_cache
     than the build and median of the largest problems, which a split shortens.  Returns
     (threads, workgroups, row_groups, split_n, max_members)."""
     import torch
-    key = f"batch3:{_arch()}:d{bt.d}:L{bt.levels}:i{iters}:{batch_signature(bt.sizes)}"
+    key = f"batch4:{_arch()}:d{bt.d}:L{bt.levels}:i{iters}:{batch_signature(bt.sizes)}"
     if use_cache:
         hit = _load_cache().get(key)
         if hit and len(hit) == 6:
