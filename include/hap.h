@@ -514,7 +514,9 @@ HAP_API hap_status hap_iterate_warm_judged(hap_ctx *ctx, const float *Y, int64_t
  * accumulate in FP32 on the matrix cores.  X, Y, T are device FP32 row-major with the given
  * row strides.  The workspace (device, 256-byte aligned, caller-owned) holds the activations of
  * `rows` rows, or what the fused kernels of small networks (n_in <= 32, hidden <= 256,
- * n_out <= 16) keep instead: hap_mlp_workspace_size bytes.  Y of hap_mlp_forward may share memory with
+ * n_out <= 16) keep instead: hap_mlp_workspace_size bytes.  Training also runs with the activations' room
+ * alone, layer by layer where the fused kernels do not fit: the same gradients and parameters, more slowly, and
+ * a loss whose FP64 squares are added in another order.  Y of hap_mlp_forward may share memory with
  * X (such a pass goes layer by layer).  Nothing synchronises the stream.
  */
 HAP_API int64_t hap_mlp_param_count(int32_t n_in, int32_t hidden, int32_t n_out); /* -1 for bad sizes */

@@ -275,8 +275,8 @@ hipError_t launch_sweep_fused(const FusedArgs<float> &a, const Launch &lc, hipSt
     } while (0)
     // several rows in flight wherever the bases and column sums of four levels fit the LDS (rows of up to
     // 4096 columns) and a workgroup's rows are staged at once
-    // (two rows of 256 threads cannot hide their latency: 3500 points, two levels 61.3 us a level one row at a
-    // time and 65.4 with both in flight, 3000 points 55 and 48)
+    // (two rows of 256 threads: 3500 points, two levels 57.3 us a level one row at a time and 65.3 with both in
+    // flight; 3200 points 57.7 and 52.7)
     const bool two_long = lc.threads == 256 && a.rb == 2 && a.n > 3250;
     if (lc.threads < 512 && a.rb <= kWin && !two_long) return launch_fused_flow(a, lc.threads, nb, tail, st);
     switch (lc.threads) {

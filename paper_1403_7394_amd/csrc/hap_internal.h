@@ -271,7 +271,8 @@ struct MlpLayout {
 };
 MlpLayout mlp_layout(int n_in, int hidden, int n_out, int64_t rows);
 // Workspace with which every path runs (at least the layout's bytes; with only those the training
-// of a batch may have to go layer by layer, which gives the same results).
+// of a batch may have to go layer by layer, with the same gradients and parameters and a loss summed in
+// another order).
 size_t mlp_workspace_bytes(int n_in, int hidden, int n_out, int64_t rows);
 hipError_t mlp_forward(const MlpLayout &lo, int n_in, int hidden, int n_out, bool bf16, const float *P,
                        const float *X, int64_t ldx, int rows, float *Y, int64_t ldy, char *ws, hipStream_t st);

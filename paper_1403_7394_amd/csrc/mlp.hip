@@ -204,8 +204,9 @@ __global__ __launch_bounds__(256) void adam_kernel(float *__restrict__ P, const 
 // rows and applies the Adam step to its parameters.
 //
 // Every product is the one mlp_gemm_kernel forms (the same MFMA, k ascending from a zero
-// accumulator, the same epilogue) and the bias gradients add in colsum_rows_kernel's order, so the
-// results are those of the layer-by-layer path bit for bit.  That path spends a step of
+// accumulator, the same epilogue) and the bias gradients add in colsum_rows_kernel's order, so outputs,
+// gradients and parameters are those of the layer-by-layer path bit for bit; the loss adds the same FP64
+// squares tile by tile, another order.  That path spends a step of
 // 32 -> 128 -> 128 -> 3 at 4096 rows (1.96 ms) in its weight gradients: a 128 x 128 product over
 // 4096 rows is four 64 x 64 tiles, four workgroups that each wait for 128 loads in turn.  The
 // chain itself (128 MFMAs of 8 passes) takes 2 us; both kernels here are bound by latency.  Measured

@@ -1163,7 +1163,8 @@ hipError_t launch_resident(const SweepArgs<T> &a, const Launch &lc, int nb, bool
 // level with its column sums: 788 points 19.8 -> 10.0 us, 2000 points 35.8 -> 20.1, 3000 points 53.2 ->
 // 36.8, 6000 points 148 -> 136, in points mode 57 -> 34 (3000) and 135 -> 115 (6000).  Rows of 8192
 // columns that read S are bound by memory either way and stay with the one-row pass, whose
-// prefetched row covers the latency without LDS traffic (240 us against 246); so do FP64 rows (4000
+// prefetched row covers the latency without LDS traffic (240 us against 246; ragged lengths above 7900 points
+// take 0.99 to 1.01 of the one-row pass at one level, 0.98 at three, and stay); so do FP64 rows (4000
 // points 125 us against 130) and workgroups of two rows of 256 threads (2500 points 47.6 us a level one row at a
 // time and 45 in flight, 3000 with four levels 54.4 and 57.9, 4000 80 and 84).
 bool flow_fits(const Launch &lc, int n, size_t elem, bool reads_s, bool tail) {

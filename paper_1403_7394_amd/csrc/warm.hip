@@ -33,7 +33,9 @@ constexpr int kScales = 6;
 // Up to 256 NV vectors the row stays in registers between the passes (NV = 0: it is read again).
 // 8192 FP32 points, the whole call: 124 us with points in random order, 281 us in a cyclic one (runs of 16
 // columns in 1024; sixteen more reads of every such row took 1334 us), 234 us with four places for all
-// points; a sorted list of sixteen per lane takes 387, 308 and 345 us.
+// points; a sorted list of sixteen per lane takes 387, 308 and 345 us.  The kernel's 110 us (2.4 TB/s) are
+// bound by vector issue, busy two thirds of the time with four waves per SIMD: 42 instructions per element, of
+// which the FP64 sums are about 20 and the passes' comparisons and the row's tail the rest.
 constexpr int kFeatThreads = 256;
 constexpr int kFeatCap = 512;   // collected values; more of them: the bound is raised until they fit
 
