@@ -1165,10 +1165,11 @@ hipError_t launch_resident(const SweepArgs<T> &a, const Launch &lc, int nb, bool
 // columns that read S are bound by memory either way and stay with the one-row pass, whose
 // prefetched row covers the latency without LDS traffic (240 us against 246; ragged lengths above 7900 points
 // take 0.99 to 1.01 of the one-row pass at one level, 0.98 at three, and stay); so do FP64 rows (4000
-// points 125 us against 130) and workgroups of two rows of 256 threads (2500 points 47.6 us a level one row at a
-// time and 45 in flight, 3000 with four levels 54.4 and 57.9, 4000 80 and 84).
-bool flow_fits(const Launch &lc, int n, size_t elem, bool reads_s, bool tail) {
-    if (lc.threads == 256 && lc.rows_per_block == 2 && reads_s && n > 2750) return false;
+// points 125 us against 130) and many workgroups of two rows of 256 threads (2500 points 47.6 us a level one row
+// at a time and 45 in flight, 3000 with four levels 54.4 and 57.9, 4000 80 and 84; row blocks of 512 rows of 4000
+// 20.6 and 18.5, of 2048 equal).
+bool flow_fits(const Launch &lc, int rows, size_t elem, bool reads_s, bool tail) {
+    if (lc.threads == 256 && lc.rows_per_block == 2 && reads_s && rows > 2750) return false;
     return elem == 4 && !lc.streaming && lc.chunks == 4 && lc.threads <= 512 && lc.rows_per_block > 1 &&
            lc.rows_per_block <= kWin && (tail || lc.threads < 512 || !reads_s);
 }
@@ -1267,7 +1268,7 @@ hipError_t launch_sweep_level(const T *S, int64_t lds, const LevelPtrs<T> &lv, T
     // with Eq. 2.7 offsets the pass reads S (no points mode)
     const bool reads_s = ex.delta != nullptr || X == nullptr;
     if constexpr (sizeof(T) == 4) {
-        if (flow_fits(lc, n, sizeof(T), reads_s, tail)) {
+        if (flow_fits(lc, a.rows, sizeof(T), reads_s, tail)) {
             if (ex.delta != nullptr) return launch_flow<T, -1>(a, lc.threads, nb, tail, ex.fits, st);
             if (X == nullptr) return launch_flow<T, 0>(a, lc.threads, nb, tail, ex.fits, st);
             if (d == 2) return launch_flow<T, 2>(a, lc.threads, nb, tail, ex.fits, st);
