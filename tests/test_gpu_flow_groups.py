@@ -69,7 +69,7 @@ def test_two_rows_are_no_slower_than_three(hap_gpu, form):
                 h.set_points(X)
             h.set_launch(128, 4, rb)
             best = float("inf")
-            for _ in range(5):
+            for _ in range(12):
                 h.profile(True)
                 h.iterate(16)
                 ms, k, _, _ = h.profile_read()
