@@ -70,6 +70,9 @@ __device__ __forceinline__ void lds_wait(const int *p, int at_least) {
 }
 
 // Second maximum after y joins (m1 the maximum before): a y that compares with nothing (NaN) is ignored.
+// v_med3_f32 does so (with a NaN among its operands it gives the least of the others, m2), but the compiler folds a
+// median with a constant -inf into a minimum, which would give m1: m1 and m2 start opaque (flow_phase1).
+// y > m1 ? m1 : fmax(m2, y) needs an instruction more (2000 points 20.2 -> 20.6 us a level, others the same).
 __device__ __forceinline__ float second_max(float m1, float m2, float y) { return __builtin_amdgcn_fmed3f(m1, m2, y); }
 __device__ __forceinline__ double second_max(double m1, double m2, double y) { return y > m1 ? m1 : fmax(m2, y); }
 
@@ -133,6 +136,7 @@ __device__ __forceinline__ void flow_phase1(FlowRow<T, NTG, NCH> &x, int i, int 
     const T zero = T(0), ninf = neg_inf<T>();
     m1 = m2 = cv = ninf;
     ck = INT_MAX;   // offset from base
+    asm("" : "+v"(m1), "+v"(m2));   // not known to be -inf: see second_max
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         asm volatile("" ::: "memory");
